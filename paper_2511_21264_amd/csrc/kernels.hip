@@ -300,6 +300,7 @@ __global__ void __launch_bounds__(64) rollout_team_kernel(RolloutArgs a0, const 
     jc.base = v3(md0.base_pos[tc.arm][0], md0.base_pos[tc.arm][1], md0.base_pos[tc.arm][2]);
     jc.bc = md0.base_cs[tc.arm][0];
     jc.bs = md0.base_cs[tc.arm][1];
+    jc.sm = seg_masks(tc.jt);
     const float *x0 = a.x0 + (a.x0_shared ? 0 : (long)j * NX);
     TeamState S;
     S.q = x0[XQ + d];
@@ -491,6 +492,7 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2, 2))
     jc.base = v3(md0.base_pos[tc.arm][0], md0.base_pos[tc.arm][1], md0.base_pos[tc.arm][2]);
     jc.bc = md0.base_cs[tc.arm][0];
     jc.bs = md0.base_cs[tc.arm][1];
+    jc.sm = seg_masks(tc.jt);
     const float *x0 = a.x0 + (a.x0_shared ? 0 : (long)j * NX);
     TeamState S;
     S.q = x0[XQ + d];

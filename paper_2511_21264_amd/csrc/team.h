@@ -104,17 +104,19 @@ __device__ __forceinline__ float row_bcast(float v)
 {
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + N, 0xF, 0xF, true));
 }
-// value of lane I of this lane's arm segment (team lane 8 * arm1 + I)
+// value of lane I of this lane's arm segment (team lane 8 * arm1 + I): the
+// second broadcast is written over the upper eight lanes of each row only
+// (DPP banks 2 and 3), so no select follows
 template <int I>
-__device__ __forceinline__ float segb(float v, bool arm1)
+__device__ __forceinline__ float segb(float v)
 {
-    const float a = row_bcast<I>(v), b = row_bcast<8 + I>(v);
-    return arm1 ? b : a;
+    const int lo = __builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + I, 0xF, 0xF, true);
+    return __int_as_float(__builtin_amdgcn_update_dpp(lo, __float_as_int(v), 0x158 + I, 0xF, 0xC, false));
 }
 template <int I>
-__device__ __forceinline__ V3 segb3(V3 v, bool arm1)
+__device__ __forceinline__ V3 segb3(V3 v)
 {
-    return v3(segb<I>(v.x, arm1), segb<I>(v.y, arm1), segb<I>(v.z, arm1));
+    return v3(segb<I>(v.x), segb<I>(v.y), segb<I>(v.z));
 }
 
 // compile-time loop: f(std::integral_constant<int, i>) for i = 0 .. N-1
@@ -129,31 +131,58 @@ __device__ __forceinline__ void static_for(F &&f)
     static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-// inclusive prefix sum over the 8-lane arm segment
-__device__ __forceinline__ float seg_prefix(float x, int jt)
+// Lane masks of the segmented scans, all ones or zero: bit pattern to AND a
+// DPP-shifted value with (a lane whose source lies outside its arm's eight
+// lanes takes 0).  Held in vector registers: as conditions they are six
+// scalar register pairs that the substep loop spills and restores, and each
+// scan step is a move, a select and an add; as masks the shift rides on the
+// AND and a step is two instructions (the same sums, bit for bit).  With the
+// two-instruction segment broadcasts, the selects of pick7 and the sparse base
+// yaw: 16.46 -> 15.77 ms per 10-iteration plan at K = 1024, H = 64 (split),
+// 4.83 -> 4.54 ms per launch at K = 4093, H = 100, 8 boxes (team).
+struct SegMask {
+    int p1, p2, p4;  // prefix: lane has a lane 1 / 2 / 4 below it in its segment
+    int s1, s2, s4;  // suffix: above it
+};
+__device__ __forceinline__ SegMask seg_masks(int jt)
 {
-    float y = dpp_shr<1>(x);
-    x += jt >= 1 ? y : 0.f;
-    y = dpp_shr<2>(x);
-    x += jt >= 2 ? y : 0.f;
-    y = dpp_shr<4>(x);
-    x += jt >= 4 ? y : 0.f;
+    SegMask m;
+    m.p1 = jt >= 1 ? -1 : 0; m.p2 = jt >= 2 ? -1 : 0; m.p4 = jt >= 4 ? -1 : 0;
+    m.s1 = jt <= 6 ? -1 : 0; m.s2 = jt <= 5 ? -1 : 0; m.s4 = jt <= 3 ? -1 : 0;
+    asm("" : "+v"(m.p1), "+v"(m.p2), "+v"(m.p4), "+v"(m.s1), "+v"(m.s2), "+v"(m.s4));
+    return m;
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_and(float v, int mask)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true) & mask);
+}
+
+// inclusive prefix sum over the 8-lane arm segment
+__device__ __forceinline__ float seg_prefix(float x, const SegMask &m)
+{
+    x += dpp_and<0x111>(x, m.p1);
+    x += dpp_and<0x112>(x, m.p2);
+    x += dpp_and<0x114>(x, m.p4);
     return x;
 }
-__device__ __forceinline__ V3 seg_prefix3(V3 v, int jt) { return v3(seg_prefix(v.x, jt), seg_prefix(v.y, jt), seg_prefix(v.z, jt)); }
+__device__ __forceinline__ V3 seg_prefix3(V3 v, const SegMask &m)
+{
+    return v3(seg_prefix(v.x, m), seg_prefix(v.y, m), seg_prefix(v.z, m));
+}
 
 // inclusive suffix sum over the 8-lane arm segment
-__device__ __forceinline__ float seg_suffix(float x, int jt)
+__device__ __forceinline__ float seg_suffix(float x, const SegMask &m)
 {
-    float y = dpp_shl<1>(x);
-    x += jt + 1 <= 7 ? y : 0.f;
-    y = dpp_shl<2>(x);
-    x += jt + 2 <= 7 ? y : 0.f;
-    y = dpp_shl<4>(x);
-    x += jt + 4 <= 7 ? y : 0.f;
+    x += dpp_and<0x101>(x, m.s1);
+    x += dpp_and<0x102>(x, m.s2);
+    x += dpp_and<0x104>(x, m.s4);
     return x;
 }
-__device__ __forceinline__ V3 seg_suffix3(V3 v, int jt) { return v3(seg_suffix(v.x, jt), seg_suffix(v.y, jt), seg_suffix(v.z, jt)); }
+__device__ __forceinline__ V3 seg_suffix3(V3 v, const SegMask &m)
+{
+    return v3(seg_suffix(v.x, m), seg_suffix(v.y, m), seg_suffix(v.z, m));
+}
 
 // sum over the 16 lanes of a team (inclusive DPP scan of the row, then a
 // broadcast of its last lane): the same value, bit for bit, in every lane
@@ -212,6 +241,7 @@ struct JointConst {
     float len, m, ix, iz;
     V3 base;
     float bc, bs;  // base yaw (cos, sin)
+    SegMask sm;
 };
 
 // the box object's world-frame inverse inertia W = R diag(1/I) R^T
@@ -276,9 +306,13 @@ __device__ inline void team_fk(const JointConst &jc, float q, int jt, JointKin &
         const M3 P = dpp_shr_m3<4>(R);
         if (jt >= 4) R = mmul(P, R);
     }
-    // base yaw
-    const M3 B = M3{{{jc.bc, -jc.bs, 0.f}, {jc.bs, jc.bc, 0.f}, {0.f, 0.f, 1.f}}};
-    R = mmul(B, R);
+    // base yaw: rows 0 and 1 mix, row 2 stays
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const float r0 = R.m[0][j], r1 = R.m[1][j];
+        R.m[0][j] = jc.bc * r0 + -jc.bs * r1;
+        R.m[1][j] = jc.bs * r0 + jc.bc * r1;
+    }
     k.z = v3(R.m[0][2], R.m[1][2], R.m[2][2]);
     if (FRAME) {
         k.x = v3(R.m[0][0], R.m[1][0], R.m[2][0]);
@@ -286,7 +320,7 @@ __device__ inline void team_fk(const JointConst &jc, float q, int jt, JointKin &
     }
     k.a = jc.ax == 0 ? v3(R.m[0][0], R.m[1][0], R.m[2][0]) : (jc.ax == 1 ? v3(R.m[0][1], R.m[1][1], R.m[2][1]) : k.z);
     const V3 d = (joint ? jc.len : 0.f) * k.z;
-    const V3 inc = seg_prefix3(d, jt);
+    const V3 inc = seg_prefix3(d, jc.sm);
     k.o1 = jc.base + inc;
     k.o = k.o1 - d;
 }
@@ -310,10 +344,10 @@ __device__ inline void team_composite(const DevModel &md, const JointConst &jc, 
 #pragma unroll
     for (int i = 0; i < 6; ++i) I[i] = joint ? I[i] : 0.f;
     // composite of links jt..6
-    const float Mc = seg_suffix(m, jt);
-    const V3 h = seg_suffix3(m * cr, jt);
+    const float Mc = seg_suffix(m, jc.sm);
+    const V3 h = seg_suffix3(m * cr, jc.sm);
 #pragma unroll
-    for (int i = 0; i < 6; ++i) I[i] = seg_suffix(I[i], jt);
+    for (int i = 0; i < 6; ++i) I[i] = seg_suffix(I[i], jc.sm);
     const V3 cc = (joint ? frcp(Mc) : 0.f) * h;
     const float c2 = dot(cc, cc);
     const S3 Ic = {I[0] - Mc * (c2 - cc.x * cc.x), I[1] - Mc * (c2 - cc.y * cc.y), I[2] - Mc * (c2 - cc.z * cc.z),
@@ -340,10 +374,9 @@ __device__ inline void team_crba(const DevModel &md, const JointConst &jc, const
     V3 K, L, mo;
     team_composite(md, jc, k, jt, K, L, mo);
     // row jt, entries c <= jt (the lower triangle the factorisation reads)
-    const bool arm1 = seg != 0;
     static_for<NJ>([&](auto ic) {
         constexpr int i = decltype(ic)::value;
-        const V3 ai = segb3<i>(k.a, arm1), mi = segb3<i>(mo, arm1);
+        const V3 ai = segb3<i>(k.a), mi = segb3<i>(mo);
         row[i] = i <= jt ? mass_entry(md, ai, mi, K, L, i == jt) : 0.f;
     });
 }
@@ -397,11 +430,10 @@ __device__ inline void team_mass_rows(const DevModel &md, const JointConst &jc, 
 // gather the packed lower triangle of the arm's Mt on every lane of its segment
 __device__ __forceinline__ void team_gather_tri(const float row[NJ], int seg, float Lp[28])
 {
-    const bool arm1 = seg != 0;
     static_for<NJ>([&](auto rc) {
         constexpr int r = decltype(rc)::value;
 #pragma unroll
-        for (int c = 0; c <= r; ++c) Lp[tri(r, c)] = segb<r>(row[c], arm1);
+        for (int c = 0; c <= r; ++c) Lp[tri(r, c)] = segb<r>(row[c]);
     });
 }
 
@@ -412,14 +444,14 @@ __device__ inline float team_rnea(const DevModel &md, const JointConst &jc, cons
     const bool joint = jt < 7;
     const float qdj = joint ? qd : 0.f;
     const V3 wa = qdj * k.a;
-    const V3 w = seg_prefix3(wa, jt);
+    const V3 w = seg_prefix3(wa, jc.sm);
     const V3 wprev = w - wa;
     const V3 ta = qdj * cross(wprev, k.a);
-    const V3 al = seg_prefix3(ta, jt);
+    const V3 al = seg_prefix3(ta, jc.sm);
     const V3 d = (joint ? jc.len : 0.f) * k.z;
     const V3 tt = cross(al, d) + cross(w, cross(w, d));
     const V3 g0 = v3(0.f, 0.f, gravity ? md.g : 0.f);
-    const V3 ao = g0 + seg_prefix3(tt, jt) - tt;
+    const V3 ao = g0 + seg_prefix3(tt, jc.sm) - tt;
     const V3 dc = 0.5f * d;
     const V3 ac = ao + cross(al, dc) + cross(w, cross(w, dc));
     const float m = joint ? jc.m : 0.f;
@@ -429,8 +461,8 @@ __device__ inline float team_rnea(const DevModel &md, const JointConst &jc, cons
     const V3 f = m * ac;
     const V3 n = joint ? Ia + cross(w, Iw) : v3(0.f, 0.f, 0.f);
     const V3 cr = k.o + dc - jc.base;
-    const V3 S = seg_suffix3(n + cross(cr, f), jt);
-    const V3 F = seg_suffix3(f, jt);
+    const V3 S = seg_suffix3(n + cross(cr, f), jc.sm);
+    const V3 F = seg_suffix3(f, jc.sm);
     return dot(k.a, S - cross(k.o - jc.base, F));
 }
 
@@ -443,12 +475,18 @@ __device__ __forceinline__ float opaque(float v)
     return v;
 }
 
-// component jt of a 7-vector held identically by the segment
+// component jt of a 7-vector held identically by the segment.  The index is
+// opaque too: its six comparisons stay here instead of being hoisted out of
+// the substep loop as scalar register pairs (which spill).
 __device__ __forceinline__ float pick7(const float v[NJ], int jt)
 {
+    asm volatile("" : "+v"(jt));
     float r = v[0];
 #pragma unroll
-    for (int i = 1; i < NJ; ++i) r = jt == i ? opaque(v[i]) : r;
+    for (int i = 1; i < NJ; ++i) {
+        const float vi = opaque(v[i]);  // outside the select: no branch around it
+        r = jt == i ? vi : r;
+    }
     return r;
 }
 
@@ -986,7 +1024,7 @@ __device__ inline void team_contact_solve(const DevModel &md, const TeamCtx &tc,
             if (arm_t) {
                 static_for<NJ>([&](auto ec) {
                     constexpr int e = decltype(ec)::value;
-                    W = fma3(Minv[e], segb3<e>(Jc[t], tc.arm != 0), W);
+                    W = fma3(Minv[e], segb3<e>(Jc[t]), W);
                 });
             }
             const V3 rt = v3(E[20 * t + 12], E[20 * t + 13], E[20 * t + 14]);
@@ -1132,7 +1170,7 @@ __device__ inline void team_contact_solve(const DevModel &md, const TeamCtx &tc,
         float dv = 0.f;
         static_for<NJ>([&](auto ec) {
             constexpr int e = decltype(ec)::value;
-            dv = fmaf(Minv[e], segb<e>(g, tc.arm != 0), dv);
+            dv = fmaf(Minv[e], segb<e>(g), dv);
         });
         if (tc.joint) v += dv;
     }
@@ -1186,7 +1224,7 @@ __device__ inline void team_dynamics(const DevModel &md, const JointConst &jc, c
     float xs[NJ];
     static_for<NJ>([&](auto ic) {
         constexpr int i = decltype(ic)::value;
-        xs[i] = segb<i>(rhs, seg != 0);
+        xs[i] = segb<i>(rhs);
     });
     chol7_solve(Lp, xs);
     v = S.qd + pick7(xs, jt);
@@ -1372,7 +1410,7 @@ __device__ inline void team_contact_solve_rows(const DevModel &md, const TeamCtx
             const V3 Jt = pick_v3(Jc, t);
             static_for<NJ>([&](auto ec) {
                 constexpr int e = decltype(ec)::value;
-                W = fma3(Minv[e], segb3<e>(Jt, tc.arm != 0), W);
+                W = fma3(Minv[e], segb3<e>(Jt), W);
             });
         }
         float *w = A + 4 * (16 * t + tc.t);
@@ -1478,7 +1516,7 @@ __device__ inline void team_contact_solve_rows(const DevModel &md, const TeamCtx
         float dv = 0.f;
         static_for<NJ>([&](auto ec) {
             constexpr int e = decltype(ec)::value;
-            dv = fmaf(Minv[e], segb<e>(g, tc.arm != 0), dv);
+            dv = fmaf(Minv[e], segb<e>(g), dv);
         });
         if (tc.joint) v += dv;
     }
