@@ -620,25 +620,23 @@ __device__ __forceinline__ void team_kin_from_lds(const float *tl, ArmKin kin[2]
         }
 }
 
-// AABB test of candidate pair p (geom A is always dynamic) after growing A
-// by margin; the same comparisons as aabb_overlap on the geoms' boxes
-__device__ __forceinline__ bool pair_overlap(const float *tl, const float *hd, int ga, int gb, float margin)
+// AABB test of a candidate pair word (ga | gb << 8; geom A is always dynamic)
+// after growing A by margin; the same comparisons as aabb_overlap on the
+// geoms' boxes, against the table the lower z alone.  No branches: geom B's
+// box is read from the team's table or the scene's by an address select, and
+// the table's entry of the former, which nothing writes, is read and ignored.
+__device__ __forceinline__ bool pair_overlap(const float *tl, const float *hd, int gab, float margin)
 {
+    const int ga = gab & 0xff, gb = gab >> 8;
     const float *A = tl + TG_AABB + 6 * ga;
-    if (gb == G_TABLE) return A[2] - margin <= 0.f;
+    const float *B = (gb >= G_BOX ? hd + HD_BOXAB - 6 * G_BOX : tl + TG_AABB) + 6 * gb;
     AABB a, b;
     a.lo = v3(A[0], A[1], A[2]);
     a.hi = v3(A[3], A[4], A[5]);
-    if (gb >= G_BOX) {
-        const float *B = hd + HD_BOXAB + 6 * (gb - G_BOX);
-        b.lo = v3(B[0], B[1], B[2]);
-        b.hi = v3(B[3], B[4], B[5]);
-    } else {
-        const float *B = tl + TG_AABB + 6 * gb;
-        b.lo = v3(B[0], B[1], B[2]);
-        b.hi = v3(B[3], B[4], B[5]);
-    }
-    return aabb_overlap(a, b, margin);
+    b.lo = v3(B[0], B[1], B[2]);
+    b.hi = v3(B[3], B[4], B[5]);
+    const bool tab = gb == G_TABLE;
+    return (tab & (a.lo.z - margin <= 0.f)) | (!tab & aabb_overlap(a, b, margin));
 }
 
 // bits of the sweeping group (G lanes starting at wave lane gshift)
@@ -659,6 +657,7 @@ __device__ inline int team_collect(const DevModel &md, float *tl, const float *h
 {
     static_assert(!TASK || G == 64, "the task forms sweep a wave wide");
     const int np = md.n_pairs;
+    constexpr int OBJ_TABLE = G_BALL | (G_TABLE << 8);
     if constexpr (G == 64) {
         // one sweep a wave: each lane runs the narrowphase of its own
         // overlapping pairs right away (no candidate list), block by block in
@@ -699,8 +698,25 @@ __device__ inline int team_collect(const DevModel &md, float *tl, const float *h
             }
             n = min((int)__popcll(gm), cap);
         }
-        auto narrow_block = [&](bool ov, int gab) {
-            if (__ballot(ov) == 0ull) return;
+        auto narrow_block = [&](bool ov, int gab, bool first) {
+            const uint64_t om = __ballot(ov);
+            if (om == 0ull) return;
+            // the ball on the table and nothing else near: pair 0 of the list,
+            // whose contact (sphere_plane) needs no dispatch on shapes
+            if (first && !box && om == 1ull && __builtin_amdgcn_readfirstlane(gab) == OBJ_TABLE) {
+                const float z = tl[TG_BALL + 2];
+                const float phi = z - hd[HD_RAD + 8];
+                if (li == 0) {
+                    ++cnt.np_tests;
+                    LL.at(0, 0) = __int_as_float(G_BALL);
+                    LL.at(0, 1) = __int_as_float(G_TABLE);
+                    LL.at(0, 2) = phi;
+                    LL.at(0, 3) = 0.f; LL.at(0, 4) = 0.f; LL.at(0, 5) = 1.f;
+                    LL.at(0, 6) = tl[TG_BALL]; LL.at(0, 7) = tl[TG_BALL + 1]; LL.at(0, 8) = 0.5f * phi;
+                }
+                n = phi < 0.f ? 1 : 0;
+                return;
+            }
             bool hit = false;
             Contact3 c;
             const int ga = gab & 0xff, gb = gab >> 8;
@@ -731,14 +747,12 @@ __device__ inline int team_collect(const DevModel &md, float *tl, const float *h
         };
         for (int base = 0; base < np; base += 2 * G) {
             const int p0 = base + li, p1 = p0 + G;
-            int g0 = 0, g1 = 0;
-            if (p0 < np) g0 = __float_as_int(hd[HD_PAIR + p0]);
-            if (p1 < np) g1 = __float_as_int(hd[HD_PAIR + p1]);
-            constexpr int OBJ_TABLE = G_BALL | (G_TABLE << 8);
-            const bool ov0 = p0 < np && !(box && g0 == OBJ_TABLE) && pair_overlap(tl, hd, g0 & 0xff, g0 >> 8, 0.f);
-            const bool ov1 = p1 < np && !(box && g1 == OBJ_TABLE) && pair_overlap(tl, hd, g1 & 0xff, g1 >> 8, 0.f);
-            narrow_block(ov0, g0);
-            narrow_block(ov1, g1);
+            const int g0 = __float_as_int(hd[HD_PAIR + min(p0, np - 1)]);
+            const int g1 = __float_as_int(hd[HD_PAIR + min(p1, np - 1)]);
+            const bool ov0 = (p0 < np) & !(box & (g0 == OBJ_TABLE)) & pair_overlap(tl, hd, g0, 0.f);
+            const bool ov1 = (p1 < np) & !(box & (g1 == OBJ_TABLE)) & pair_overlap(tl, hd, g1, 0.f);
+            narrow_block(ov0, g0, base == 0);
+            narrow_block(ov1, g1, false);
         }
         return n;
     }
@@ -748,11 +762,10 @@ __device__ inline int team_collect(const DevModel &md, float *tl, const float *h
     // candidates still land in pair order
     for (int base = 0; base < np; base += 2 * G) {
         const int p0 = base + li, p1 = p0 + G;
-        int g0 = 0, g1 = 0;
-        if (p0 < np) g0 = __float_as_int(hd[HD_PAIR + p0]);
-        if (p1 < np) g1 = __float_as_int(hd[HD_PAIR + p1]);
-        const bool ov0 = p0 < np && pair_overlap(tl, hd, g0 & 0xff, g0 >> 8, 0.f);
-        const bool ov1 = p1 < np && pair_overlap(tl, hd, g1 & 0xff, g1 >> 8, 0.f);
+        const int g0 = __float_as_int(hd[HD_PAIR + min(p0, np - 1)]);
+        const int g1 = __float_as_int(hd[HD_PAIR + min(p1, np - 1)]);
+        const bool ov0 = (p0 < np) & pair_overlap(tl, hd, g0, 0.f);
+        const bool ov1 = (p1 < np) & pair_overlap(tl, hd, g1, 0.f);
         const uint64_t below = (1ull << li) - 1ull;
         const uint64_t m0 = group_bits<G>(__ballot(ov0), gshift), m1 = group_bits<G>(__ballot(ov1), gshift);
         if (ov0) cand[ncand + __popcll(m0 & below)] = g0;
@@ -1537,7 +1550,10 @@ __device__ inline void team_finish(const DevModel &md, const TeamCtx &tc, TeamSt
     float W[9];
     if (box) obj_world_inv_inertia(md, S.quat, W);
     if (!box && ball_only_contact(tc.LL, nc)) {
-        ball_contact_solve(md, tc.LL, S.pb, vb, wb);
+        if (__float_as_int(tc.LL.at(0, 1)) == G_TABLE)
+            table_contact_solve(md, tc.LL.at(0, 2), tc.LL.at(0, 8) - S.pb.z, vb, wb);
+        else
+            ball_contact_solve(md, tc.LL, S.pb, vb, wb);
     } else if (ROWS && nc > 0 && nc <= 4) {
         if (PRIO) __builtin_amdgcn_s_setprio(2);
         team_contact_solve_rows<NC, TASK>(md, tc, k, S.pb, nc, v, vb, wb, W);
@@ -1639,7 +1655,7 @@ __device__ inline void team_stage_cost(const DevModel &md, const JointConst &jc,
         const int p = first_pair + i;
         const int gab = __float_as_int(tc.hd[HD_PAIR + p]);
         const int ga = gab & 0xff, gb = gab >> 8;
-        if (pair_overlap(tl, tc.hd, ga, gb, md.m_c)) {
+        if (pair_overlap(tl, tc.hd, gab, md.m_c)) {
             const Shape A = team_geom(tl, tc.hd, ga), B = team_geom(tl, tc.hd, gb);
             if (tc.count) {
                 ++cnt.np_tests;

@@ -1,0 +1,42 @@
+"""The ball's contact with the table alone, which the kernels solve by a path of its own (its sweep skips the
+narrowphase dispatch, its solve the products by the normal's zeros): one substep against the FP64 oracle over depths,
+velocities, spins, friction and sweep counts, without boxes and with the most boxes a scene holds (three blocks of
+candidate pairs).  Tolerance: 1e-5 of each state group's largest magnitude, the one-substep parity bound."""
+import numpy as np
+import pytest
+
+import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("mapping", ["lane", "team", "wave", "split"])
+@pytest.mark.parametrize("boxes,mu,n_pgs", [(0, 1.0, 20), (3, 0.3, 20), (16, 1.7, 1)])
+def test_one_substep_with_the_ball_on_the_table(oracle_mod, mapping, boxes, mu, n_pgs):
+    import paper_2511_21264_amd as mp
+    ctx = mp.Context(0)
+    sc = W.make_scene(2, n_box=boxes, mu=mu, n_pgs=n_pgs)
+    scene, o = mp.Scene(ctx, sc), oracle_mod.Oracle(sc)
+    n = 70
+    rng = np.random.default_rng(17)
+    X = np.tile(W.initial_state(sc), (n, 1))
+    X[:, 14:28] = rng.uniform(-0.3, 0.3, (n, 14))
+    X[:, 44] = sc["ball_r"] - rng.uniform(-0.0005, 0.004, n)  # a few stay above the table
+    X[:, 49:52] = rng.uniform(-1.0, 1.0, (n, 3))
+    X[:, 52:55] = rng.uniform(-5.0, 5.0, (n, 3))
+    X = X.astype(np.float32)
+    U = rng.uniform(-1.0, 1.0, (n, 1, 14)).astype(np.float32)
+    out = torch.zeros((n, 55), device="cuda")
+    mp.mppi_simulate(ctx, scene, torch.tensor(X, device="cuda"), torch.tensor(U, device="cuda"), X_out=out, n_sub=1,
+                     mapping=mapping)
+    got = out.cpu().numpy().astype(np.float64)
+    ones = 0
+    for i in range(n):
+        want, nc = o.substep(X[i].astype(np.float64), U[i, 0].astype(np.float64))
+        ones += nc == 1
+        for a, b in ((0, 14), (14, 28), (28, 42), (42, 45), (45, 49), (49, 52), (52, 55)):
+            scale = max(np.abs(want[a:b]).max(), 1e-3)
+            assert np.abs(got[i, a:b] - want[a:b]).max() <= 1e-5 * scale, (i, a, nc)
+    assert n > ones > n // 2
+    ctx.close()
