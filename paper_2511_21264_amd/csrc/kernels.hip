@@ -334,7 +334,7 @@ __global__ void __launch_bounds__(64) rollout_team_kernel(RolloutArgs a0, const 
         }
         for (int s = 0; s < nsub; ++s)
             team_substep<NC, TPW == 1 ? 64 : TEAM, TPW == 1, TASK>(model(a.md), jc, tc, S, u, cnt);
-        team_stage_cost<false, TASK>(model(a.md), jc, tc, S, u, uprev, k == 0, hist, dist, a.K, acc, cnt);
+        team_stage_cost<false, TASK, TPW == 1>(model(a.md), jc, tc, S, u, uprev, k == 0, hist, dist, a.K, acc, cnt);
         uprev = u;
         if (a.xout && a.traj && active && primary) {
             float *o = a.xout + ((long)j * a.H + k) * NX;

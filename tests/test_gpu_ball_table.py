@@ -40,3 +40,27 @@ def test_one_substep_with_the_ball_on_the_table(oracle_mod, mapping, boxes, mu, 
             assert np.abs(got[i, a:b] - want[a:b]).max() <= 1e-5 * scale, (i, a, nc)
     assert n > ones > n // 2
     ctx.close()
+
+
+@pytest.mark.parametrize("boxes,spread", [(0, 0.9), (3, 0.6), (16, 0.6), (16, 0.05)])
+def test_coarse_test_of_the_team_form_misses_no_pair(boxes, spread):
+    """The four-samples-a-wave form skips its sweeps when joined boxes rule every pair out; one sample a wave always
+    sweeps.  Random arm poses (arms against boxes, table, ball and each other, some states far from everything)
+    give the same bits in both, states, costs and every cost term."""
+    import paper_2511_21264_amd as mp
+    ctx = mp.Context(0)
+    sc = W.make_scene(3, n_box=boxes)
+    scene = mp.Scene(ctx, sc)
+    n, H = 253, 3
+    X = torch.tensor(W.random_states(sc, n, seed=9, spread=spread).astype(np.float32), device="cuda")
+    U = torch.tensor(W.random_controls(n, H, 4).astype(np.float32), device="cuda")
+    got = {}
+    for m in ("team", "wave", "split"):
+        got[m] = [torch.zeros(s, device="cuda") for s in ((n,), (n, mp.NTERMS), (n, 55))]
+        mp.mppi_simulate(ctx, scene, X, U, got[m][0], got[m][1], got[m][2], mapping=m)
+    for m in ("wave", "split"):
+        for a, b in zip(got["team"], got[m]):
+            assert torch.equal(a, b)
+    if spread > 0.5 and boxes:  # the poses do reach the boxes
+        assert (got["team"][1][:, 5] > 0).sum() >= boxes // 2
+    ctx.close()
