@@ -163,6 +163,8 @@ int build_model(const mppi_scene_desc *d, DevModel &m)
         }
     }
     m.pad_rad = (float)d->pad_rad;
+    m.r_max = m.pad_rad;
+    for (int i = 0; i < 6; ++i) m.r_max = std::max(m.r_max, m.link_rad[i]);
     m.ball_r = (float)d->ball_r;
     m.ball_m = (float)d->ball_m;
     m.inv_ball_m = (float)(1.0 / d->ball_m);

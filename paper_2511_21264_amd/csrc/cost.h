@@ -25,7 +25,10 @@
 // without a narrowphase.  So only pairs closer than m_c need last step's
 // distance: a per-lane bitmask records which pairs were closer than m_c at
 // the previous step and their distances sit in a per-sample global array
-// touched only for those pairs.
+// touched only for those pairs.  In the one-lane form the bits sit in the
+// lane's park area: word a * 7 + g bit b for arm geom and box, then two words
+// of arm 1 geom x arm 2 geom, bit 7 g + g2; they are all zero, and not
+// touched, while no lane of the wave has a pair that the arms' bounds leave.
 #pragma once
 #include "step.h"
 
@@ -48,7 +51,7 @@ __device__ __forceinline__ float rot_angle(const float *Rt, V3 c0, V3 c1, V3 c2)
 }
 
 // the further terms at the post-step state (added to t[7..16])
-__device__ inline void ext_terms(const DevModel &md, const ArmKin kin[2], const float x[NX], CostAcc &acc)
+__device__ __forceinline__ void ext_terms(const DevModel &md, const ArmKin kin[2], const float x[NX], CostAcc &acc)
 {
     float home = 0.f;
 #pragma unroll
@@ -100,12 +103,6 @@ __device__ __forceinline__ float total_cost(const DevModel &md, CostAcc &acc)
     return c;
 }
 
-// bit set: pair closer than m_c at the previous control step
-struct DistHist {
-    uint32_t box[14];  // arm geom (7 * arm + g) x box bit b
-    uint32_t aa[2];    // arm 1 geom x arm 2 geom, bit 7 g + g2
-};
-
 __device__ __forceinline__ void dist_term(const DevModel &md, float d, bool has_prev, uint32_t prev_word,
                                           uint32_t bit, float *slot, uint32_t &new_word, CostAcc &acc)
 {
@@ -124,9 +121,9 @@ __device__ __forceinline__ void dist_term(const DevModel &md, float d, bool has_
 // dist: per-sample history slots, pair-major with stride `stride` (= lanes of
 // the launch).  TASK: the form that can evaluate the further terms.
 template <bool TASK>
-__device__ inline void stage_cost(const DevModel &md, const float x[NX], const float u[NU], const float uprev[NU],
-                                  bool first, DistHist &hist, float *dist, long stride, CostAcc &acc,
-                                  StepCounters &cnt)
+__device__ __forceinline__ void stage_cost(const DevModel &md, const float x[NX], const float u[NU], const float uprev[NU],
+                                  bool first, const LanePark &pk, bool &any_prev, float *dist, long stride,
+                                  CostAcc &acc, StepCounters &cnt)
 {
     ArmKin kin[2];
     fk_arm(md, 0, x + XQ, kin[0]);
@@ -151,54 +148,77 @@ __device__ inline void stage_cost(const DevModel &md, const float x[NX], const f
         }
         acc.t[4] += sm;
     }
-    // collision distances: arm geoms x boxes, then arm 1 x arm 2
-    Shape arm[2][7];
-    AABB barm[2][7];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int gg = 0; gg < 7; ++gg) {
-            arm[a][gg] = arm_shape(md, kin[a], gg);
-            barm[a][gg] = shape_aabb(arm[a][gg]);
-        }
+    // collision distances: arm geoms x boxes, then arm 1 x arm 2; pairs that
+    // the arms' bounds rule out in every lane of the wave are at the saturated
+    // distance (any_prev: the history words were written by the step before)
     const int nb = md.n_box;
     const bool has_prev = !first;
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int gg = 0; gg < 7; ++gg) {
-            const int row = 7 * a + gg;
-            uint32_t nw = 0u;
-            for (int b = 0; b < nb; ++b) {
-                const Shape bx = box_shape(md, b);
-                if (aabb_overlap(barm[a][gg], shape_aabb(bx), md.m_c)) {
-                    ++cnt.np_tests;
-                    if (gg < 6) ++cnt.box_tests;
-                    const float d = narrow(arm[a][gg], bx).phi;
-                    dist_term(md, d, has_prev, hist.box[row], 1u << b, dist + (long)(row * nb + b) * stride, nw, acc);
+    const float mc = md.m_c;
+    const AABB u0 = arm_bound(kin[0], md.r_max), u1 = arm_bound(kin[1], md.r_max);
+    const bool haa = any_lane(aabb_overlap(u0, u1, mc));
+    uint32_t mb0 = 0u, mb1 = 0u;
+#pragma unroll 1
+    for (int b = 0; b < nb; ++b) {
+        const AABB bx = shape_aabb(box_shape(md, b));
+        mb0 |= any_lane(aabb_overlap(u0, bx, mc)) ? 1u << b : 0u;
+        mb1 |= any_lane(aabb_overlap(u1, bx, mc)) ? 1u << b : 0u;
+    }
+    if (haa | ((mb0 | mb1) != 0u)) {
+        park_points(pk, kin);
+#pragma unroll 1
+        for (int row = 0; row < 14; ++row) {
+            const int a = row < 7 ? 0 : 1, gg = row < 7 ? row : row - 7;
+            const uint32_t pw = any_prev ? __float_as_uint(pk.at(PK_H + row)) : 0u;
+            uint32_t nw = 0u, m = a == 0 ? mb0 : mb1;
+            if (m != 0u) {
+                const Shape s = parked_shape(md, pk, a, gg);
+                const AABB bs = shape_aabb(s);
+#pragma unroll 1
+                for (; m; m &= m - 1u) {
+                    const int b = __builtin_ctz(m);
+                    const Shape bx = box_shape(md, b);
+                    if (aabb_overlap(bs, shape_aabb(bx), mc)) {
+                        ++cnt.np_tests;
+                        if (gg < 6) ++cnt.box_tests;
+                        const float d = narrow(s, bx).phi;
+                        dist_term(md, d, has_prev, pw, 1u << b, dist + (long)(row * nb + b) * stride, nw, acc);
+                    }
                 }
             }
-            hist.box[row] = nw;
+            pk.at(PK_H + row) = __uint_as_float(nw);
         }
-    const int off = 14 * nb;
-    uint32_t nw0 = 0u, nw1 = 0u;
-#pragma unroll
-    for (int gg = 0; gg < 7; ++gg)
-#pragma unroll
-        for (int g2 = 0; g2 < 7; ++g2) {
-            if (aabb_overlap(barm[0][gg], barm[1][g2], md.m_c)) {
-                ++cnt.np_tests;
-                const float d = narrow(arm[0][gg], arm[1][g2]).phi;
-                const int idx = 7 * gg + g2;
-                if (idx < 32)
-                    dist_term(md, d, has_prev, hist.aa[0], 1u << idx, dist + (long)(off + idx) * stride, nw0, acc);
-                else
-                    dist_term(md, d, has_prev, hist.aa[1], 1u << (idx - 32), dist + (long)(off + idx) * stride, nw1,
-                              acc);
+        const int off = 14 * nb;
+        const uint32_t pw0 = any_prev ? __float_as_uint(pk.at(PK_H + 14)) : 0u;
+        const uint32_t pw1 = any_prev ? __float_as_uint(pk.at(PK_H + 15)) : 0u;
+        uint32_t nw0 = 0u, nw1 = 0u;
+        if (haa) {
+#pragma unroll 1
+            for (int gg = 0; gg < 7; ++gg) {
+                const Shape s = parked_shape(md, pk, 0, gg);
+                const AABB bs = shape_aabb(s);
+                if (!any_lane(aabb_overlap(bs, u1, mc))) continue;
+#pragma unroll 1
+                for (int g2 = 0; g2 < 7; ++g2) {
+                    const Shape s2 = parked_shape(md, pk, 1, g2);
+                    if (aabb_overlap(bs, shape_aabb(s2), mc)) {
+                        ++cnt.np_tests;
+                        const float d = narrow(s, s2).phi;
+                        const int idx = 7 * gg + g2;
+                        uint32_t nw = 0u;
+                        dist_term(md, d, has_prev, idx < 32 ? pw0 : pw1, 1u << (idx & 31),
+                                  dist + (long)(off + idx) * stride, nw, acc);
+                        nw0 |= idx < 32 ? nw : 0u;
+                        nw1 |= idx < 32 ? 0u : nw;
+                    }
+                }
             }
         }
-    hist.aa[0] = nw0;
-    hist.aa[1] = nw1;
+        pk.at(PK_H + 14) = __uint_as_float(nw0);
+        pk.at(PK_H + 15) = __uint_as_float(nw1);
+        any_prev = true;
+    } else {
+        any_prev = false;
+    }
     if (TASK && md.ext) ext_terms(md, kin, x, acc);
 }
 

@@ -58,6 +58,7 @@ struct DevModel {
     float apos[2][3], ax_t[2];
     float arotR[2][9];  // per-arm orientation targets as rotation matrices, row-major
     float orot[4];      // object orientation target (w, x, y, z), unit
+    float r_max;        // largest radius among the arm geoms
 };
 
 }  // namespace mppi

@@ -16,6 +16,22 @@
 
 namespace mppi {
 
+// The model's words are re-read inside the horizon loop rather than hoisted:
+// hoisted, ~100 uniform values overflow the SGPRs into VGPRs.  The pointer is
+// opaque (so the reads stay where they are) and goes through the constant
+// address space: the model is read-only during a launch, so uniform reads
+// become scalar loads through the scalar cache instead of vector loads.
+__device__ __forceinline__ const DevModel &model(const DevModel *p)
+{
+    // (uniform; said to the compiler, which may hold it in vector registers across a call)
+    const uint64_t v = (uint64_t)p;
+    const uint64_t u = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
+                       (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+    const __attribute__((address_space(4))) DevModel *c = (const __attribute__((address_space(4))) DevModel *)u;
+    asm volatile("" : "+s"(c));
+    return *(const DevModel *)c;
+}
+
 struct V3 {
     float x, y, z;
 };
@@ -80,7 +96,7 @@ __device__ __forceinline__ void rot_cols(float R[3][3], float c, float s)
     }
 }
 
-__device__ inline void fk_arm(const DevModel &md, int arm, const float *q, ArmKin &k)
+__device__ __forceinline__ void fk_arm(const DevModel &md, int arm, const float *q, ArmKin &k)
 {
     float R[3][3] = {{md.base_cs[arm][0], -md.base_cs[arm][1], 0.f},
                      {md.base_cs[arm][1], md.base_cs[arm][0], 0.f},
@@ -116,7 +132,7 @@ __device__ inline void fk_arm(const DevModel &md, int arm, const float *q, ArmKi
 __device__ __forceinline__ constexpr int tri(int r, int c) { return r * (r + 1) / 2 + c; }
 
 // Mt = M(q) + diag(diag_add), packed lower triangle (28 floats)
-__device__ inline void crba_arm(const DevModel &md, int arm, const ArmKin &k, float Mt[28])
+__device__ __forceinline__ void crba_arm(const DevModel &md, int arm, const ArmKin &k, float Mt[28])
 {
     float mc = 0.f;
     V3 cc = v3(0.f, 0.f, 0.f);
@@ -173,7 +189,7 @@ __device__ __forceinline__ void half_angle_sincos(float a, float &c, float &s_ov
 // in-place Cholesky of a packed SPD 7x7 (lower); pivots stay > 0 because
 // the armature is on the diagonal.  The diagonal slots receive 1 / L_jj, so
 // that the solves multiply instead of dividing.
-__device__ inline void chol7(float L[28])
+__device__ __forceinline__ void chol7(float L[28])
 {
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
@@ -193,7 +209,7 @@ __device__ inline void chol7(float L[28])
 }
 
 // x = (L L^T)^-1 b, in place (L from chol7: reciprocal diagonal)
-__device__ inline void chol7_solve(const float L[28], float x[NJ])
+__device__ __forceinline__ void chol7_solve(const float L[28], float x[NJ])
 {
 #pragma unroll
     for (int i = 0; i < NJ; ++i) {
@@ -214,7 +230,7 @@ __device__ inline void chol7_solve(const float L[28], float x[NJ])
 // bias torques c(q, qd) (+ gravity when gravity != 0), qdd = 0.  The forward
 // pass keeps only each link's force m a_c and moment I al + w x I w about its
 // centre; the backward pass accumulates them towards the base.
-__device__ inline void rnea_bias_arm(const DevModel &md, int arm, const ArmKin &k, const float *qd, bool gravity,
+__device__ __forceinline__ void rnea_bias_arm(const DevModel &md, int arm, const ArmKin &k, const float *qd, bool gravity,
                                      float tau[NJ])
 {
     V3 f[NJ], nm[NJ];

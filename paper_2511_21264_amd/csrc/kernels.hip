@@ -35,18 +35,6 @@ __device__ __forceinline__ void sample_u(const float *nu_k, const float *sig_k, 
     for (int d = 0; d < NU; ++d) u[d] = clampf(fmaf(sig_k[d], z[d], nu_k[d]), -umax, umax);
 }
 
-// The model's words are re-read inside the horizon loop rather than hoisted:
-// hoisted, ~100 uniform values overflow the SGPRs into VGPRs.  The pointer is
-// opaque (so the reads stay where they are) and goes through the constant
-// address space: the model is read-only during a launch, so uniform reads
-// become scalar loads through the scalar cache instead of vector loads.
-__device__ __forceinline__ const DevModel &model(const DevModel *p)
-{
-    const __attribute__((address_space(4))) DevModel *c = (const __attribute__((address_space(4))) DevModel *)p;
-    asm volatile("" : "+s"(c));
-    return *(const DevModel *)c;
-}
-
 // Scene of this workgroup: the single scene of the launch, or an entry of a
 // packed table (uneven batches: block b covers block blk[2b+1] of scene blk[2b]).
 __device__ __forceinline__ void block_scene(const RolloutArgs &a0, const RolloutArgs *tab, const int *blk, int m,
@@ -84,10 +72,7 @@ __global__ void __launch_bounds__(64) rollout_kernel(RolloutArgs a0, const Rollo
 #pragma unroll
     for (int i = 0; i < NX; ++i) x[i] = x0[i];
     const int nsub = a.n_sub > 0 ? a.n_sub : md.n_sub;
-    DistHist hist;
-#pragma unroll
-    for (int i = 0; i < 14; ++i) hist.box[i] = 0u;
-    hist.aa[0] = hist.aa[1] = 0u;
+    bool any_prev = false;
     float *dist = a.dist + j;
     CostAcc acc;
 #pragma unroll
@@ -107,7 +92,7 @@ __global__ void __launch_bounds__(64) rollout_kernel(RolloutArgs a0, const Rollo
                      (uint32_t)k, (uint32_t)a.m, u);
         }
         for (int s = 0; s < nsub; ++s) substep<NC, TASK>(model(a.md), x, u, LL, pk, cnt);
-        stage_cost<TASK>(model(a.md), x, u, uprev, k == 0, hist, dist, a.K, acc, cnt);
+        stage_cost<TASK>(model(a.md), x, u, uprev, k == 0, pk, any_prev, dist, a.K, acc, cnt);
 #pragma unroll
         for (int d = 0; d < NU; ++d) uprev[d] = u[d];
         if (a.xout && a.traj) {
@@ -161,7 +146,7 @@ __global__ void __launch_bounds__(64) rollout_step_kernel(RolloutArgs a, float *
     const LanePark pk{lds + NC * CL_FIELDS * blockDim.x, (int)threadIdx.x, (int)blockDim.x};
     float x[NX], uprev[NU];
     CostAcc acc;
-    DistHist hist;
+    bool any_prev = k > 0;
     StepCounters cnt;
     if (k == 0) {
         const float *x0 = a.x0 + (a.x0_shared ? 0 : (long)j * NX);
@@ -171,9 +156,6 @@ __global__ void __launch_bounds__(64) rollout_step_kernel(RolloutArgs a, float *
         for (int d = 0; d < NU; ++d) uprev[d] = 0.f;
 #pragma unroll
         for (int i = 0; i < NTERMS; ++i) acc.t[i] = 0.f;
-#pragma unroll
-        for (int i = 0; i < 14; ++i) hist.box[i] = 0u;
-        hist.aa[0] = hist.aa[1] = 0u;
         cnt = {0, 0, 0, 0};
     } else {
 #pragma unroll
@@ -183,9 +165,7 @@ __global__ void __launch_bounds__(64) rollout_step_kernel(RolloutArgs a, float *
 #pragma unroll
         for (int i = 0; i < NTERMS; ++i) acc.t[i] = TASK || i < 7 ? ps[(PS_ACC + i) * K + j] : 0.f;
 #pragma unroll
-        for (int i = 0; i < 14; ++i) hist.box[i] = __float_as_uint(ps[(PS_HIST + i) * K + j]);
-        hist.aa[0] = __float_as_uint(ps[(PS_HIST + 14) * K + j]);
-        hist.aa[1] = __float_as_uint(ps[(PS_HIST + 15) * K + j]);
+        for (int i = 0; i < 16; ++i) pk.at(PK_H + i) = ps[(PS_HIST + i) * K + j];
         cnt.contacts = __float_as_int(ps[(PS_CNT + 0) * K + j]);
         cnt.np_tests = __float_as_int(ps[(PS_CNT + 1) * K + j]);
         cnt.box_tests = __float_as_int(ps[(PS_CNT + 2) * K + j]);
@@ -203,7 +183,7 @@ __global__ void __launch_bounds__(64) rollout_step_kernel(RolloutArgs a, float *
                  (uint32_t)k, (uint32_t)a.m, u);
     }
     for (int s = 0; s < nsub; ++s) substep<NC, TASK>(model(a.md), x, u, LL, pk, cnt);
-    stage_cost<TASK>(model(a.md), x, u, uprev, k == 0, hist, dist, a.K, acc, cnt);
+    stage_cost<TASK>(model(a.md), x, u, uprev, k == 0, pk, any_prev, dist, a.K, acc, cnt);
     if (a.xout && a.traj) {
         float *o = a.xout + ((long)j * a.H + k) * NX;
 #pragma unroll
@@ -217,9 +197,7 @@ __global__ void __launch_bounds__(64) rollout_step_kernel(RolloutArgs a, float *
 #pragma unroll
         for (int i = 0; i < (TASK ? NTERMS : 7); ++i) ps[(PS_ACC + i) * K + j] = acc.t[i];
 #pragma unroll
-        for (int i = 0; i < 14; ++i) ps[(PS_HIST + i) * K + j] = __uint_as_float(hist.box[i]);
-        ps[(PS_HIST + 14) * K + j] = __uint_as_float(hist.aa[0]);
-        ps[(PS_HIST + 15) * K + j] = __uint_as_float(hist.aa[1]);
+        for (int i = 0; i < 16; ++i) ps[(PS_HIST + i) * K + j] = any_prev ? pk.at(PK_H + i) : 0.f;
         ps[(PS_CNT + 0) * K + j] = __int_as_float(cnt.contacts);
         ps[(PS_CNT + 1) * K + j] = __int_as_float(cnt.np_tests);
         ps[(PS_CNT + 2) * K + j] = __int_as_float(cnt.box_tests);
@@ -253,8 +231,11 @@ __global__ void __launch_bounds__(64) rollout_step_kernel(RolloutArgs a, float *
 // run on a clamped sample index so that every lane reaches every barrier;
 // they write nothing.
 // TASK (one wave per sample only): the box object and the further terms
+// Two waves per SIMD at the least: a task form left to itself takes 280
+// registers, which halves the waves in flight (tray pick, K = 4096, H = 16:
+// 4.2 ms per launch against 2.9).
 template <int NC, int TPW, bool TASK = false>
-__global__ void __launch_bounds__(64) rollout_team_kernel(RolloutArgs a0, const RolloutArgs *tab, const int *blk, int m)
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) rollout_team_kernel(RolloutArgs a0, const RolloutArgs *tab, const int *blk, int m)
 {
     extern __shared__ float lds[];
     RolloutArgs a;

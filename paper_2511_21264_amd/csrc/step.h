@@ -105,17 +105,6 @@ __device__ __forceinline__ void try_obj_contact(const DevModel &md, const LaneLi
     }
 }
 
-__device__ __forceinline__ Shape arm_shape(const DevModel &md, const ArmKin &k, int g)
-{
-    Shape s;
-    if (g < 6) {
-        s.type = SH_CAPSULE; s.p0 = k.o[g]; s.p1 = k.o[g + 1]; s.r = md.link_rad[g];
-    } else {
-        s.type = SH_SPHERE; s.p0 = k.o[NJ]; s.p1 = s.p0; s.r = md.pad_rad;
-    }
-    return s;
-}
-
 __device__ __forceinline__ Shape box_shape(const DevModel &md, int b)
 {
     Shape s;
@@ -140,26 +129,90 @@ __device__ __forceinline__ Shape ball_shape(const DevModel &md, V3 pb)
     return s;
 }
 
-// sweep every candidate pair in canonical order; returns the contact count.
-// BOX: the object is the box of pose o (pb unused)
-template <bool BOX>
-__device__ inline int collect_contacts(const DevModel &md, const ArmKin kin[2], V3 pb, const ObjPose &o,
-                                       const LaneList &L, StepCounters &cnt)
+// Per-lane area in LDS for data that only the rarer paths re-read: both arms'
+// Cholesky factors (the arm-contact path), the joint origins and tips (the
+// pair sweeps, whose rolled loops index them), and the distance-history bits
+// of the cost's pairs.  Layout [field][lane].
+constexpr int PK_L = 0;          // 2 x 28 packed factors
+constexpr int PK_P = 56;         // 2 x 8 x 3 joint origins o_0..o_6 and tip
+constexpr int PK_H = 104;        // 14 words arm geom x box, 2 words arm 1 geom x arm 2 geom
+constexpr int PK_FIELDS = 120;
+struct LanePark {
+    float *base;
+    int lane;
+    int width;
+    __device__ __forceinline__ float &at(int f) const { return base[f * width + lane]; }
+};
+
+// arm geom g from the parked joint origins (a, g uniform over the wave)
+__device__ __forceinline__ Shape parked_shape(const DevModel &md, const LanePark &pk, int a, int g)
 {
-    int n = 0;
-    const Shape ball = ball_shape(md, pb), table = table_shape();
-    const AABB bball = shape_aabb(ball), btab = shape_aabb(table);
-    Shape arm[2][7];
-    AABB barm[2][7];
+    Shape s;
+    const bool cap = g < 6;
+    const int f0 = PK_P + 3 * (8 * a + (cap ? g : 7)), f1 = PK_P + 3 * (8 * a + (cap ? g + 1 : 7));
+    s.type = cap ? SH_CAPSULE : SH_SPHERE;
+    s.p0 = v3(pk.at(f0), pk.at(f0 + 1), pk.at(f0 + 2));
+    s.p1 = v3(pk.at(f1), pk.at(f1 + 1), pk.at(f1 + 2));
+    s.r = cap ? md.link_rad[g] : md.pad_rad;
+    return s;
+}
+
+__device__ __forceinline__ void park_points(const LanePark &pk, const ArmKin kin[2])
+{
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int g = 0; g < 7; ++g) {
-            arm[a][g] = arm_shape(md, kin[a], g);
-            barm[a][g] = shape_aabb(arm[a][g]);
+        for (int i = 0; i <= NJ; ++i) {
+            const int f = PK_P + 3 * (8 * a + i);
+            pk.at(f) = kin[a].o[i].x;
+            pk.at(f + 1) = kin[a].o[i].y;
+            pk.at(f + 2) = kin[a].o[i].z;
         }
+}
+
+// a box that holds every geom of an arm: the joint origins and tip grown by
+// the largest radius.  Every geom's own AABB lies within it (rounding is
+// monotone), so what it misses no geom overlaps.
+__device__ __forceinline__ AABB arm_bound(const ArmKin &k, float rmax)
+{
+    V3 lo = k.o[0], hi = k.o[0];
+#pragma unroll
+    for (int i = 1; i <= NJ; ++i) {
+        lo = v3(fminf(lo.x, k.o[i].x), fminf(lo.y, k.o[i].y), fminf(lo.z, k.o[i].z));
+        hi = v3(fmaxf(hi.x, k.o[i].x), fmaxf(hi.y, k.o[i].y), fmaxf(hi.z, k.o[i].z));
+    }
+    AABB b;
+    b.lo = v3(lo.x - rmax, lo.y - rmax, lo.z - rmax);
+    b.hi = v3(hi.x + rmax, hi.y + rmax, hi.z + rmax);
+    return b;
+}
+__device__ __forceinline__ AABB join(const AABB &a, const AABB &b)
+{
+    AABB c;
+    c.lo = v3(fminf(a.lo.x, b.lo.x), fminf(a.lo.y, b.lo.y), fminf(a.lo.z, b.lo.z));
+    c.hi = v3(fmaxf(a.hi.x, b.hi.x), fmaxf(a.hi.y, b.hi.y), fmaxf(a.hi.z, b.hi.z));
+    return c;
+}
+__device__ __forceinline__ bool any_lane(bool p) { return __ballot(p) != 0ull; }
+
+// Sweep of the candidate pairs in canonical order; returns the contact count.
+// BOX: the object is the box of pose o (pb unused).  Groups of pairs that the
+// arms' bounds rule out in every lane of the wave are skipped (in the common
+// case all of them: only the ball and the table meet); the others go through
+// rolled loops over the parked joint origins.  Unrolled over the pairs, with
+// every geom's AABB in private arrays, the sweep was two thirds of a 130 KB
+// kernel that the instruction cache does not hold, and its arrays lived in
+// scratch memory.
+template <bool BOX>
+__device__ __forceinline__ int collect_contacts(const DevModel &md, const ArmKin kin[2], V3 pb, const ObjPose &o,
+                                       const LaneList &L, const LanePark &pk, StepCounters &cnt)
+{
+    int n = 0;
+    const Shape ball = ball_shape(md, pb), table = table_shape();
+    const AABB bobj = BOX ? o.bb : shape_aabb(ball);
+    // 1 object-table
     if (BOX) {
-        // 1 object-table: the vertices below the plane, four at most
+        // the vertices below the plane, four at most
         if (o.bb.lo.z < 0.f) {
             ++cnt.np_tests;
             int taken = 0;
@@ -176,73 +229,100 @@ __device__ inline int collect_contacts(const DevModel &md, const ArmKin kin[2], 
                 }
             }
         }
-        // 2 object-pads, 3 object-links, 4 object-boxes
+    } else if (n < md.n_cmax && bobj.lo.z <= 0.f) {
+        ++cnt.np_tests;
+        const Contact3 c = sphere_plane(pb, ball.r);
+        if (c.phi < 0.f) push_contact(L, n, G_BALL, G_TABLE, c);
+    }
+    // what the bounds leave, for the whole wave
+    const int nb = md.n_box;
+    const float rmax = md.r_max;
+    const AABB u0 = arm_bound(kin[0], rmax), u1 = arm_bound(kin[1], rmax);
+    float z0 = kin[0].o[1].z, z1 = kin[1].o[1].z;  // geoms 1..6: from the second origin on
 #pragma unroll
-        for (int a = 0; a < 2; ++a) try_obj_contact(md, L, n, cnt, G_ARM + 7 * a + 6, o, arm[a][6], barm[a][6]);
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int g = 0; g < 6; ++g) try_obj_contact(md, L, n, cnt, G_ARM + 7 * a + g, o, arm[a][g], barm[a][g]);
-        for (int b = 0; b < md.n_box; ++b) {
-            const Shape bx = box_shape(md, b);
-            try_obj_contact(md, L, n, cnt, G_BOX + b, o, bx, shape_aabb(bx));
-        }
-    } else {
-        // 1 ball-table
-        try_contact(md, L, n, cnt, G_BALL, G_TABLE, ball, table, bball, btab);
-        // 2 ball-pads
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-            try_contact(md, L, n, cnt, G_BALL, G_ARM + 7 * a + 6, ball, arm[a][6], bball, barm[a][6]);
-        // 3 ball-links
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int g = 0; g < 6; ++g)
-                try_contact(md, L, n, cnt, G_BALL, G_ARM + 7 * a + g, ball, arm[a][g], bball, barm[a][g]);
-        // 4 ball-boxes
-        for (int b = 0; b < md.n_box; ++b) {
-            const Shape bx = box_shape(md, b);
-            try_contact(md, L, n, cnt, G_BALL, G_BOX + b, ball, bx, bball, shape_aabb(bx));
+    for (int i = 2; i <= NJ; ++i) {
+        z0 = fminf(z0, kin[0].o[i].z);
+        z1 = fminf(z1, kin[1].o[i].z);
+    }
+    const bool ho0 = any_lane(aabb_overlap(bobj, u0, 0.f)), ho1 = any_lane(aabb_overlap(bobj, u1, 0.f));
+    const bool ht0 = any_lane(z0 - rmax <= 0.f), ht1 = any_lane(z1 - rmax <= 0.f);
+    const bool haa = any_lane(aabb_overlap(u0, u1, 0.f));
+    const AABB all = join(join(u0, u1), bobj);
+    uint32_t mb0 = 0u, mb1 = 0u, mbo = 0u;
+#pragma unroll 1
+    for (int b = 0; b < nb; ++b) {
+        const AABB bx = shape_aabb(box_shape(md, b));
+        if (any_lane(aabb_overlap(all, bx, 0.f))) {
+            mbo |= any_lane(aabb_overlap(bobj, bx, 0.f)) ? 1u << b : 0u;
+            mb0 |= any_lane(aabb_overlap(u0, bx, 0.f)) ? 1u << b : 0u;
+            mb1 |= any_lane(aabb_overlap(u1, bx, 0.f)) ? 1u << b : 0u;
         }
     }
-    // 5 arm geoms 2..7 - table
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int g = 1; g < 7; ++g)
-            try_contact(md, L, n, cnt, G_ARM + 7 * a + g, G_TABLE, arm[a][g], table, barm[a][g], btab);
-    // 6 arm geoms - boxes
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int g = 0; g < 7; ++g)
-            for (int b = 0; b < md.n_box; ++b) {
+    if (ho0 | ho1 | ht0 | ht1 | haa | ((mb0 | mb1 | mbo) != 0u)) {
+        park_points(pk, kin);
+        // 2 object-pads, 3 object-links
+#pragma unroll 1
+        for (int i = 0; i < 14; ++i) {
+            const int a = i < 2 ? i : (i < 8 ? 0 : 1), g = i < 2 ? 6 : (i < 8 ? i - 2 : i - 8);
+            if (a == 0 ? !ho0 : !ho1) continue;
+            const Shape s = parked_shape(md, pk, a, g);
+            if (BOX)
+                try_obj_contact(md, L, n, cnt, G_ARM + 7 * a + g, o, s, shape_aabb(s));
+            else
+                try_contact(md, L, n, cnt, G_BALL, G_ARM + 7 * a + g, ball, s, bobj, shape_aabb(s));
+        }
+        // 4 object-boxes
+#pragma unroll 1
+        for (uint32_t m = mbo; m; m &= m - 1u) {
+            const int b = __builtin_ctz(m);
+            const Shape bx = box_shape(md, b);
+            if (BOX)
+                try_obj_contact(md, L, n, cnt, G_BOX + b, o, bx, shape_aabb(bx));
+            else
+                try_contact(md, L, n, cnt, G_BALL, G_BOX + b, ball, bx, bobj, shape_aabb(bx));
+        }
+        // 5 arm geoms 2..7 - table
+#pragma unroll 1
+        for (int i = 0; i < 12; ++i) {
+            const int a = i < 6 ? 0 : 1, g = 1 + (i < 6 ? i : i - 6);
+            if (a == 0 ? !ht0 : !ht1) continue;
+            const Shape s = parked_shape(md, pk, a, g);
+            try_contact(md, L, n, cnt, G_ARM + 7 * a + g, G_TABLE, s, table, shape_aabb(s), shape_aabb(table));
+        }
+        // 6 arm geoms - boxes
+#pragma unroll 1
+        for (int i = 0; i < 14; ++i) {
+            const int a = i < 7 ? 0 : 1, g = i < 7 ? i : i - 7;
+            uint32_t m = a == 0 ? mb0 : mb1;
+            if (m == 0u) continue;
+            const Shape s = parked_shape(md, pk, a, g);
+            const AABB bs = shape_aabb(s);
+#pragma unroll 1
+            for (; m; m &= m - 1u) {
+                const int b = __builtin_ctz(m);
                 const Shape bx = box_shape(md, b);
-                try_contact(md, L, n, cnt, G_ARM + 7 * a + g, G_BOX + b, arm[a][g], bx, barm[a][g], shape_aabb(bx));
+                try_contact(md, L, n, cnt, G_ARM + 7 * a + g, G_BOX + b, s, bx, bs, shape_aabb(bx));
             }
-    // 7 arm 1 - arm 2
-#pragma unroll
-    for (int g = 0; g < 7; ++g)
-#pragma unroll
-        for (int g2 = 0; g2 < 7; ++g2)
-            try_contact(md, L, n, cnt, G_ARM + g, G_ARM + 7 + g2, arm[0][g], arm[1][g2], barm[0][g], barm[1][g2]);
+        }
+        // 7 arm 1 - arm 2
+        if (haa) {
+#pragma unroll 1
+            for (int g = 0; g < 7; ++g) {
+                const Shape s = parked_shape(md, pk, 0, g);
+                const AABB bs = shape_aabb(s);
+                if (!any_lane(aabb_overlap(bs, u1, 0.f))) continue;
+#pragma unroll 1
+                for (int g2 = 0; g2 < 7; ++g2) {
+                    const Shape s2 = parked_shape(md, pk, 1, g2);
+                    try_contact(md, L, n, cnt, G_ARM + g, G_ARM + 7 + g2, s, s2, bs, shape_aabb(s2));
+                }
+            }
+        }
+    }
     if (n >= md.n_cmax) ++cnt.overflow;
     cnt.contacts += n;
     return n;
 }
-
-// Per-lane spill area in LDS for data that only the (rare) arm-contact path
-// re-reads: both arms' Cholesky factors and joint axes.  Layout [field][lane].
-constexpr int PK_L = 0;          // 2 x 28 packed factors
-constexpr int PK_A = 56;         // 2 x 7 x 3 joint axes
-constexpr int PK_FIELDS = 98;
-struct LanePark {
-    float *base;
-    int lane;
-    int width;
-    __device__ __forceinline__ float &at(int f) const { return base[f * width + lane]; }
-};
 
 // bodies touching at a contact, from its geom ids: arm index (-1 none) and link of each side
 struct Sides {
@@ -269,17 +349,13 @@ __device__ __forceinline__ float jac_coef(const Sides &s, int a, int j)
     return (((s.armA == a) & (j <= s.linkA)) ? 1.f : 0.f) - (((s.armB == a) & (j <= s.linkB)) ? 1.f : 0.f);
 }
 
-// arm part of the 3 x 14 relative point Jacobian at p (axes from the park area)
-__device__ __forceinline__ void arm_jac(const ArmKin kin[2], const LanePark &pk, const Sides &s, V3 p, V3 J[14])
+// arm part of the 3 x 14 relative point Jacobian at p
+__device__ __forceinline__ void arm_jac(const ArmKin kin[2], const Sides &s, V3 p, V3 J[14])
 {
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            const int f = PK_A + 3 * (7 * a + j);
-            const V3 ax = v3(pk.at(f), pk.at(f + 1), pk.at(f + 2));
-            J[7 * a + j] = jac_coef(s, a, j) * cross(ax, p - kin[a].o[j]);
-        }
+        for (int j = 0; j < NJ; ++j) J[7 * a + j] = jac_coef(s, a, j) * cross(kin[a].a[j], p - kin[a].o[j]);
 }
 
 __device__ __forceinline__ void solve_parked(const LanePark &pk, int a, float x[NJ])
@@ -348,7 +424,7 @@ struct Slots {
 
 // BOX: the object's inverse inertia is W (world frame, row-major), else 1/I_b
 template <int NC, bool BOX = false>
-__device__ inline void contact_solve(const DevModel &md, const ArmKin kin[2], const LanePark &pk, V3 pb,
+__device__ __forceinline__ void contact_solve(const DevModel &md, const ArmKin kin[2], const LanePark &pk, V3 pb,
                                      const LaneList &LL, int nc, float v[14], V3 &vb, V3 &wb,
                                      const float *W = nullptr)
 {
@@ -395,7 +471,7 @@ __device__ inline void contact_solve(const DevModel &md, const ArmKin kin[2], co
                 // Mt^-1 J_t^T, one column per Cartesian row of J_t
                 float Wx[14], Wy[14], Wz[14];
                 V3 Jt[14];
-                arm_jac(kin, pk, st, S.r[t] + pb, Jt);
+                arm_jac(kin, st, S.r[t] + pb, Jt);
 #pragma unroll
                 for (int d = 0; d < 14; ++d) {
                     Wx[d] = Jt[d].x;
@@ -420,7 +496,7 @@ __device__ inline void contact_solve(const DevModel &md, const ArmKin kin[2], co
                         const Sides ss = contact_sides(S.gab[s]);
                         if ((ss.armA >= 0) | (ss.armB >= 0)) {
                             V3 Js[14];
-                            arm_jac(kin, pk, ss, S.r[s] + pb, Js);
+                            arm_jac(kin, ss, S.r[s] + pb, Js);
                             float G[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                             for (int d = 0; d < 14; ++d) {
@@ -501,7 +577,7 @@ __device__ inline void contact_solve(const DevModel &md, const ArmKin kin[2], co
                 const Sides ss = contact_sides(S.gab[s]);
                 if ((ss.armA >= 0) | (ss.armB >= 0)) {
                     V3 Js[14];
-                    arm_jac(kin, pk, ss, S.r[s] + pb, Js);
+                    arm_jac(kin, ss, S.r[s] + pb, Js);
 #pragma unroll
                     for (int d = 0; d < 14; ++d) gimp[d] += dot(Js[d], S.P[s]);
                 }
@@ -514,6 +590,41 @@ __device__ inline void contact_solve(const DevModel &md, const ArmKin kin[2], co
             for (int j = 0; j < NJ; ++j) v[7 * a + j] += gimp[7 * a + j];
         }
     }
+}
+
+// The general solve as a call: it keeps some 320 values per contact list in
+// registers and private memory, and inlined its live ranges push the common
+// path's state out of the registers (and fill the instruction cache).  The
+// kinematics and velocities go through copies made here, so that only this
+// path takes their address; the model pointer is uniform and goes back to
+// scalar registers.  Everything else is inlined: as a call, the substep took
+// its state and the model through memory.  With that and the rolled, bounded
+// sweeps a launch of K = 65536, H = 64 went from 22.0 to 8.1 ms (14.1 with the
+// sweeps alone).
+template <int NC, bool BOX>
+__device__ __attribute__((noinline)) void contact_solve_call(const DevModel *mp, const ArmKin *kin, const LanePark pk,
+                                                             V3 pb, const LaneList LL, int nc, float *v, V3 *vb,
+                                                             V3 *wb, const float *W)
+{
+    contact_solve<NC, BOX>(model(mp), kin, pk, pb, LL, nc, v, *vb, *wb, W);
+}
+template <int NC, bool BOX>
+__device__ __forceinline__ void contact_solve_out(const DevModel &md, const ArmKin kin[2], const LanePark &pk, V3 pb,
+                                                  const LaneList &LL, int nc, float v[14], V3 &vb, V3 &wb,
+                                                  const float *W)
+{
+    ArmKin k2[2] = {kin[0], kin[1]};
+    float v2[14], W2[9];
+#pragma unroll
+    for (int i = 0; i < 14; ++i) v2[i] = v[i];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) W2[i] = BOX ? W[i] : 0.f;
+    V3 vb2 = vb, wb2 = wb;
+    contact_solve_call<NC, BOX>(&md, k2, pk, pb, LL, nc, v2, &vb2, &wb2, W2);
+#pragma unroll
+    for (int i = 0; i < 14; ++i) v[i] = v2[i];
+    vb = vb2;
+    wb = wb2;
 }
 
 // Projected Gauss-Seidel on four rows (one contact), f = 0 at the start:
@@ -555,7 +666,7 @@ __device__ __forceinline__ void pgs4(const float a[16], const float b[4], const 
 // and its branch-free pair test: 16.5 -> 15.8 ms per 10-iteration plan at
 // K = 1024, H = 64 (split); 4.75 -> 4.28 ms per launch at K = 4093, H = 100
 // (team).
-__device__ inline void table_contact_solve(const DevModel &md, float phi, float rz, V3 &vb, V3 &wb)
+__device__ __forceinline__ void table_contact_solve(const DevModel &md, float phi, float rz, V3 &vb, V3 &wb)
 {
     const float im = md.inv_ball_m, iI = md.inv_ball_I, mu = md.mu;
     const float d = rz * rz;
@@ -591,7 +702,7 @@ __device__ inline void table_contact_solve(const DevModel &md, float phi, float 
 // One contact of the ball with a static body (table or box), the common case:
 // the whole solve in registers (in the team mappings identically on every
 // lane of the team).
-__device__ inline void ball_contact_solve(const DevModel &md, const LaneList &LL, V3 pb, V3 &vb, V3 &wb)
+__device__ __forceinline__ void ball_contact_solve(const DevModel &md, const LaneList &LL, V3 pb, V3 &vb, V3 &wb)
 {
     const V3 n = v3(LL.at(0, 3), LL.at(0, 4), LL.at(0, 5));
     const V3 r = v3(LL.at(0, 6), LL.at(0, 7), LL.at(0, 8)) - pb;
@@ -626,8 +737,33 @@ __device__ inline void ball_contact_solve(const DevModel &md, const LaneList &LL
     wb = fma3(md.inv_ball_I, cross(r, P), wb);
 }
 
+// kinematics, inertia and its factor (parked), bias forces and free joint
+// velocities of one arm
+__device__ __forceinline__ void arm_free_velocities(const DevModel &md, int a, const float *q, const float *qd,
+                                                    const float *qdes, const float *u, ArmKin &kin,
+                                                    const LanePark &pk, float *v)
+{
+    fk_arm(md, a, q, kin);
+    float L[28];
+    crba_arm(md, a, kin, L);
+    chol7(L);
+    float c[NJ];
+    rnea_bias_arm(md, a, kin, qd, md.gravcomp == 0, c);
+    float rhs[NJ];
+#pragma unroll
+    for (int i = 0; i < NJ; ++i) {
+        const float tau = clampf(md.kp * (qdes[i] - q[i]) + md.kd * (u[i] - qd[i]), -md.tau_max, md.tau_max);
+        rhs[i] = md.h * (tau - md.damp * qd[i] - c[i]);
+    }
+    chol7_solve(L, rhs);
+#pragma unroll
+    for (int i = 0; i < NJ; ++i) v[i] = qd[i] + rhs[i];
+#pragma unroll
+    for (int i = 0; i < 28; ++i) pk.at(PK_L + 28 * a + i) = L[i];
+}
+
 template <int NC, bool BOX = false>
-__device__ inline void substep(const DevModel &md, float x[NX], const float u[NU], const LaneList &LL,
+__device__ __forceinline__ void substep(const DevModel &md, float x[NX], const float u[NU], const LaneList &LL,
                                const LanePark &pk, StepCounters &cnt)
 {
     const float h = md.h;
@@ -635,41 +771,12 @@ __device__ inline void substep(const DevModel &md, float x[NX], const float u[NU
     for (int i = 0; i < 14; ++i) x[XQDES + i] = fmaf(h, u[i], x[XQDES + i]);
     ArmKin kin[2];
     float v[14];
+    arm_free_velocities(md, 0, x + XQ, x + XQD, x + XQDES, u, kin[0], pk, v);
+    // keep the two arms' dynamics sequential: their live sets would
+    // otherwise be interleaved by the scheduler and double the registers
 #pragma unroll
-    for (int a = 0; a < 2; ++a) {
-        if (a == 1) {
-            // keep the two arms' dynamics sequential: their live sets would
-            // otherwise be interleaved by the scheduler and double the registers
-#pragma unroll
-            for (int i = 7; i < 14; ++i) asm volatile("" : "+v"(x[XQ + i]) : "v"(v[6]));
-        }
-        fk_arm(md, a, x + XQ + 7 * a, kin[a]);
-        float L[28];
-        crba_arm(md, a, kin[a], L);
-        chol7(L);
-        float c[NJ];
-        rnea_bias_arm(md, a, kin[a], x + XQD + 7 * a, md.gravcomp == 0, c);
-        float rhs[NJ];
-#pragma unroll
-        for (int i = 0; i < NJ; ++i) {
-            const int d = 7 * a + i;
-            const float qd = x[XQD + d];
-            const float tau = clampf(md.kp * (x[XQDES + d] - x[XQ + d]) + md.kd * (u[d] - qd), -md.tau_max, md.tau_max);
-            rhs[i] = h * (tau - md.damp * qd - c[i]);
-        }
-        chol7_solve(L, rhs);
-#pragma unroll
-        for (int i = 0; i < NJ; ++i) v[7 * a + i] = x[XQD + 7 * a + i] + rhs[i];
-        // park the factor and the joint axes for the contact path
-#pragma unroll
-        for (int i = 0; i < 28; ++i) pk.at(PK_L + 28 * a + i) = L[i];
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            pk.at(PK_A + 3 * (7 * a + j)) = kin[a].a[j].x;
-            pk.at(PK_A + 3 * (7 * a + j) + 1) = kin[a].a[j].y;
-            pk.at(PK_A + 3 * (7 * a + j) + 2) = kin[a].a[j].z;
-        }
-    }
+    for (int i = 7; i < 14; ++i) asm volatile("" : "+v"(x[XQ + i]) : "v"(v[6]));
+    arm_free_velocities(md, 1, x + XQ + 7, x + XQD + 7, x + XQDES + 7, u + 7, kin[1], pk, v + 7);
     const V3 pb = v3(x[XPB], x[XPB + 1], x[XPB + 2]);
     V3 vb = v3(x[XVB], x[XVB + 1], x[XVB + 2] - h * md.g);
     V3 wb = v3(x[XWB], x[XWB + 1], x[XWB + 2]);
@@ -693,18 +800,18 @@ __device__ inline void substep(const DevModel &md, float x[NX], const float u[NU
         const V3 Lb = v3(md.obj_I[0] * wbb.x, md.obj_I[1] * wbb.y, md.obj_I[2] * wbb.z);
         const V3 gb = cross(wbb, Lb);
         wb = wb - h * mulR(o.R, v3(md.obj_iI[0] * gb.x, md.obj_iI[1] * gb.y, md.obj_iI[2] * gb.z));
-        const int nc = collect_contacts<true>(md, kin, pb, o, LL, cnt);
-        if (nc > 0) contact_solve<NC, true>(md, kin, pk, pb, LL, nc, v, vb, wb, W);
+        const int nc = collect_contacts<true>(md, kin, pb, o, LL, pk, cnt);
+        if (nc > 0) contact_solve_out<NC, true>(md, kin, pk, pb, LL, nc, v, vb, wb, W);
     } else {
         ObjPose o0;
-        const int nc = collect_contacts<false>(md, kin, pb, o0, LL, cnt);
+        const int nc = collect_contacts<false>(md, kin, pb, o0, LL, pk, cnt);
         const bool ball1 = nc == 1 && __float_as_int(LL.at(0, 0)) == G_BALL;
         if (ball1 && __float_as_int(LL.at(0, 1)) == G_TABLE)
             table_contact_solve(md, LL.at(0, 2), LL.at(0, 8) - pb.z, vb, wb);
         else if (ball1 && __float_as_int(LL.at(0, 1)) >= G_BOX)
             ball_contact_solve(md, LL, pb, vb, wb);
         else if (nc > 0)
-            contact_solve<NC>(md, kin, pk, pb, LL, nc, v, vb, wb);
+            contact_solve_out<NC, false>(md, kin, pk, pb, LL, nc, v, vb, wb, nullptr);
     }
 
 #pragma unroll

@@ -78,7 +78,7 @@ constexpr int HD_FIELDS = HD_RAD + 12;
 // blocks G_st (NC x NC x 9), row matrix A (4NC x 4NC), b, 1/(A_rr + R_r), R,
 // and the multipliers when several contacts are active
 constexpr int tcs_fields(int nc) { return 20 * nc + 9 * nc * nc + 16 * nc * nc + 16 * nc; }
-constexpr int PK_FIELDS4 = (PK_FIELDS + 3) / 4 * 4;  // park area rounded to 16 bytes
+constexpr int PK_FIELDS4 = 100; // park area: both arms' factors
 constexpr int team_lds_floats(int nc) { return TG_FIELDS + nc * CL_FIELDS + PK_FIELDS4 + tcs_fields(nc); }
 // 16-byte alignment of the park and solve areas (float4 reads and writes)
 static_assert(HD_FIELDS % 4 == 0 && TG_FIELDS % 4 == 0 && (4 * CL_FIELDS) % 4 == 0 && PK_L % 4 == 0 &&
@@ -774,7 +774,7 @@ __device__ inline int team_collect(const DevModel &md, float *tl, const float *h
                     LL.at(0, 3) = 0.f; LL.at(0, 4) = 0.f; LL.at(0, 5) = 1.f;
                     LL.at(0, 6) = tl[TG_BALL]; LL.at(0, 7) = tl[TG_BALL + 1]; LL.at(0, 8) = 0.5f * phi;
                 }
-                n = phi < 0.f ? 1 : 0;
+                n = min(phi < 0.f ? 1 : 0, md.n_cmax);
                 return;
             }
             bool hit = false;
@@ -1325,9 +1325,9 @@ __device__ inline int team_contacts(const DevModel &md, const TeamCtx &tc, const
         // sphere_plane forms it
         if (__ballot(team_coarse<false>(md, tc.hd, k, pb, tc.jt, tc.t, 0.f)) == 0ull) {
             const float phi = pb.z - tc.hd[HD_RAD + 8];
-            const int nc = phi < 0.f ? 1 : 0;
+            const int nc = min(phi < 0.f ? 1 : 0, md.n_cmax);
             if (tc.t == 0) {
-                if (phi <= 0.f) {
+                if (phi <= 0.f && md.n_cmax > 0) {
                     ++cnt.np_tests;
                     tc.LL.at(0, 0) = __int_as_float(G_BALL);
                     tc.LL.at(0, 1) = __int_as_float(G_TABLE);

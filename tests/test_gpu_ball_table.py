@@ -12,11 +12,12 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("mapping", ["lane", "team", "wave", "split"])
-@pytest.mark.parametrize("boxes,mu,n_pgs", [(0, 1.0, 20), (3, 0.3, 20), (16, 1.7, 1)])
-def test_one_substep_with_the_ball_on_the_table(oracle_mod, mapping, boxes, mu, n_pgs):
+@pytest.mark.parametrize("boxes,mu,n_pgs,n_cmax", [(0, 1.0, 20, 4), (3, 0.3, 20, 4), (16, 1.7, 1, 4), (3, 1.0, 20, 1),
+                                                   (3, 1.0, 20, 0)])
+def test_one_substep_with_the_ball_on_the_table(oracle_mod, mapping, boxes, mu, n_pgs, n_cmax):
     import paper_2511_21264_amd as mp
     ctx = mp.Context(0)
-    sc = W.make_scene(2, n_box=boxes, mu=mu, n_pgs=n_pgs)
+    sc = W.make_scene(2, n_box=boxes, mu=mu, n_pgs=n_pgs, n_cmax=n_cmax)
     scene, o = mp.Scene(ctx, sc), oracle_mod.Oracle(sc)
     n = 70
     rng = np.random.default_rng(17)
@@ -38,7 +39,7 @@ def test_one_substep_with_the_ball_on_the_table(oracle_mod, mapping, boxes, mu, 
         for a, b in ((0, 14), (14, 28), (28, 42), (42, 45), (45, 49), (49, 52), (52, 55)):
             scale = max(np.abs(want[a:b]).max(), 1e-3)
             assert np.abs(got[i, a:b] - want[a:b]).max() <= 1e-5 * scale, (i, a, nc)
-    assert n > ones > n // 2
+    assert n > ones > n // 2 if n_cmax else ones == 0
     ctx.close()
 
 
