@@ -552,14 +552,16 @@ static int qp_check(const mppi_qp *qp, int H)
     return MPPI_OK;
 }
 
-// (I + rho A^T A)^-1 for A = [I; D1; D2; L] on H steps, in double, stored as
-// float rows of stride S (zero padded) in the context's QP slot.
+// (I + rho A^T A)^-1 for A = [I; D1; D2; L] on H steps, formed in double, in
+// the context's QP slot: rho times it as H x H doubles (the tile form splits
+// those), then as float rows of stride S (zero padded).
 static int qp_matrix(mppi_ctx *ctx, int H, double rho, hipStream_t stream, const float **out, int *S)
 {
     const int st = ((H + 3) & ~3) + 4;
     void *dp;
     int rc;
-    if ((rc = ensure(ctx, S_QPP, (size_t)H * st * sizeof(float), &dp))) return rc;
+    const size_t dbl = (size_t)H * H * sizeof(double);
+    if ((rc = ensure(ctx, S_QPP, dbl + (size_t)H * st * sizeof(float), &dp))) return rc;
     if (ctx->qp_H != H || ctx->qp_rho != rho || ctx->qp_S != st) {
         std::vector<double> M((size_t)H * H, 0.0);
         auto add_row = [&](const std::vector<std::pair<int, double>> &row) {
@@ -587,7 +589,7 @@ static int qp_matrix(mppi_ctx *ctx, int H, double rho, hipStream_t stream, const
             }
         }
         std::vector<float> P((size_t)H * st, 0.f);
-        std::vector<double> x(H);
+        std::vector<double> x(H), D((size_t)H * H);
         for (int c = 0; c < H; ++c) {
             for (int i = 0; i < H; ++i) {  // C y = e_c
                 double v = i == c ? 1.0 : 0.0;
@@ -599,16 +601,20 @@ static int qp_matrix(mppi_ctx *ctx, int H, double rho, hipStream_t stream, const
                 for (int k = i + 1; k < H; ++k) v -= C[(size_t)k * H + i] * x[k];
                 x[i] = v / C[(size_t)i * H + i];
             }
-            for (int i = 0; i < H; ++i) P[(size_t)i * st + c] = (float)x[i];
+            for (int i = 0; i < H; ++i) {
+                P[(size_t)i * st + c] = (float)x[i];
+                D[(size_t)i * H + c] = rho * x[i];
+            }
         }
         // work queued on this stream may still read the previous matrix
         HIPCHK(hipStreamSynchronize(stream));
-        HIPCHK(hipMemcpy(dp, P.data(), P.size() * sizeof(float), hipMemcpyHostToDevice));
+        HIPCHK(hipMemcpy(dp, D.data(), dbl, hipMemcpyHostToDevice));
+        HIPCHK(hipMemcpy((char *)dp + dbl, P.data(), P.size() * sizeof(float), hipMemcpyHostToDevice));
         ctx->qp_H = H;
         ctx->qp_rho = rho;
         ctx->qp_S = st;
     }
-    *out = (const float *)dp;
+    *out = (const float *)((const char *)dp + dbl);
     *S = st;
     return MPPI_OK;
 }
@@ -617,6 +623,7 @@ static void qp_args(ProjectArgs &pa, const mppi_scene *scene, const mppi_qp *qp,
 {
     const double dt = scene->host.h * scene->host.n_sub;
     pa.P = P;
+    pa.rhoP = (const double *)P - (size_t)H * H;
     pa.S = S;
     pa.K = K;
     pa.H = H;

@@ -106,6 +106,7 @@ void launch_stats(const StatsArgs &a, hipStream_t s);
 // joint, one horizon step per lane; H <= 64)
 struct ProjectArgs {
     const float *P;         // [H][S] (I + rho A^T A)^-1, rows padded with zeros to S floats
+    const double *rhoP;     // [H][H] rho times the same, in double (right before P)
     int S;                  // row stride of P: a multiple of 4, >= H rounded up to 4
     const float *U_in;      // [K][H][14] samples, or null: nu + sigma * z from the Philox counters
     float *U_out;           // [K][H][14] projected samples

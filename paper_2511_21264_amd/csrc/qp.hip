@@ -12,7 +12,9 @@
 //     z' = clip(a + w, lo, hi);   w += a - z';   z = z'
 // from z = clip(A v~), w = 0; the output is v clipped to the velocity box.
 //
-// Mapping: one workgroup per sample, one wave per joint (14 waves), one
+// Two forms, by sample count and horizon (launch_project): one wave per
+// sixteen sequences (project_tile_kernel), and
+// one workgroup per sample, one wave per joint (14 waves), one
 // horizon step per lane for H <= 64 and two (steps k and k + 64) for
 // H <= 128.  A v and A^T y are DPP whole-wave shifts and
 // scans (neighbour differences, prefix and suffix sums).  The dense product
@@ -293,8 +295,353 @@ __global__ void __launch_bounds__(14 * 64) project_kernel(ProjectArgs a)
         if (act[h]) a.U_out[((long)j * H + k + 64 * h) * NU + d] = clipf(v[h], -a.u_max, a.u_max);
 }
 
+// ---------------------------------------------------------------------------
+// Tile form: one wave per sixteen sequences (consecutive joint sequences, the
+// samples one after another), the whole iteration in its registers.  The MFMA
+// 16x16x4 result puts sequence l % 16 on lane l and, of every 16-row block, the
+// four rows 4 (l / 16) .. + 3.  Since the rows and columns of P may be taken
+// in any order, block b, element v of lane group q is given step
+// R q + 4 b + v (R = 4 NB steps a group, H <= 16 NB): a lane then holds R
+// consecutive steps of one sequence, so the scans and differences of A v and
+// A^T y are serial adds in registers plus a few values from the neighbouring
+// groups, and the right-hand side of a column step (step i of every group) is
+// already an MFMA's B operand.  Nothing passes between waves, so there is no
+// barrier.
+//   The product is formed in bf16 MFMAs 16x16x32 from three parts of each
+// factor (24 bits and more: P's parts come from double), six partial products,
+// accumulated in FP32.  An FP32 MFMA and vector instructions do not overlap
+// here, not even from two waves (4 NB^2 MFMAs of 32 cycles came on top of the
+// rest: 152 us), the bf16 ones do: 114 us.  Its error and the scans' against
+// FP64 over the whole iteration is smaller than the FP32 form's: 4.9e-6 of the
+// result's norm against 5.6e-6 at H = 64, 5.6e-6 against 6.8e-6 at H = 128
+// (the block offsets in double bring it from 6.9e-6 and 9.7e-6, for 13 %).
+// Bound by vector instructions, about 50 a step and iteration, at one wave per
+// SIMD (K = 1024: 896 waves).  K = 1024, H = 64, 60 iterations: 250 us (a
+// workgroup per sample) -> 130 us; K = 4096: 986 -> 356 us; K = 1024, H = 24:
+// 240 -> 69 us; K = 1024, H = 100: 583 -> 289 us.  P's parts are in LDS in
+// operand order, 24 KB at H = 64 and 96 KB at H = 128 for a workgroup of four
+// waves.
+// two floats as three bf16 parts each, rounded to nearest; the parts' sums are
+// the floats exactly (up to denormals)
+typedef __bf16 h2 __attribute__((ext_vector_type(2)));
+typedef float f2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void split3(float x0, float x1, uint32_t p[3])
+{
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+        p[t] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{x0, x1}, h2));
+        x0 -= __uint_as_float(p[t] << 16);
+        x1 -= __uint_as_float(p[t] & 0xffff0000u);
+    }
+}
+
+template <int NB, bool FULL>
+__global__ void __launch_bounds__(256, NB <= 4 ? 2 : 1) project_tile_kernel(ProjectArgs a)
+{
+    constexpr int R = 4 * NB;
+    constexpr int KS = (R + 7) / 8;  // product steps of eight columns a group
+    typedef __bf16 h8 __attribute__((ext_vector_type(8)));
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    extern __shared__ __align__(16) unsigned short PA[];  // [row block][product step][part][lane][8]
+    const int H = a.H;
+    for (int e = threadIdx.x; e < NB * KS * 512; e += 256) {
+        const int c = e & 7, l = (e >> 3) & 63, w = e >> 9;
+        const int rb = w / KS, i = 8 * (w % KS) + c;
+        const int row = R * ((l & 15) >> 2) + 4 * rb + (l & 3), col = R * (l >> 4) + i;
+        double p = (i < R && row < H && col < H) ? a.rhoP[row * H + col] : 0.0;
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            const __bf16 b = (__bf16)(float)p;
+            PA[((w * 3 + t) * 64 + l) * 8 + c] = __builtin_bit_cast(unsigned short, b);
+            p -= (double)(float)b;
+        }
+    }
+    __syncthreads();
+    const int lane = threadIdx.x & 63, q = lane >> 4;
+    const long nseq = (long)a.K * NU;
+    const long seq_raw = ((long)blockIdx.x * 4 + (threadIdx.x >> 6)) * 16 + (lane & 15);
+    if (seq_raw - (lane & 15) >= nseq) return;  // no barrier follows
+    const bool live = seq_raw < nseq;
+    const long seq = live ? seq_raw : nseq - 1;
+    const int j = (int)(seq / NU), d = (int)(seq - (long)j * NU);
+    const int s0 = R * q;  // this lane's first step
+    // values of the neighbouring groups through the LDS crossbar (lanes l -+ 16 k)
+    const int dn1 = ((lane - 16) & 63) << 2, dn2 = ((lane - 32) & 63) << 2, dn3 = ((lane - 48) & 63) << 2;
+    const int up1 = ((lane + 16) & 63) << 2, up2 = dn2, up3 = dn1;
+    auto from = [](int addr, float v) { return __int_as_float(__builtin_amdgcn_ds_bpermute(addr, __float_as_int(v))); };
+    const bool h1 = q >= 1, h2 = q >= 2, h3 = q >= 3;  // groups below this one
+    const bool g1 = q <= 2, g2 = q <= 1, g3 = q == 0;  // groups above
+    auto present = [&](int i) { return FULL || s0 + i < H; };
+    float pos_lo = a.pos_lo[0], pos_hi = a.pos_hi[0];
+#pragma unroll
+    for (int e = 1; e < NU; ++e) {
+        pos_lo = d == e ? a.pos_lo[e] : pos_lo;
+        pos_hi = d == e ? a.pos_hi[e] : pos_hi;
+    }
+    const float q0 = a.x0[(a.x0_shared ? 0 : (long)j * NX) + XQDES + d];
+    const float loL = (pos_lo - q0) / a.dt, hiL = (pos_hi - q0) / a.dt;
+    const float um = a.u_max, da = a.dacc, dj = a.djerk;
+    float vt[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const int st = s0 + i;
+        vt[i] = 0.f;
+        if (present(i)) {
+            if (a.U_in) {
+                vt[i] = a.U_in[((long)j * H + st) * NU + d];
+            } else {
+                const float z = normal_joint(a.key0, a.key1, (uint32_t)j, (uint32_t)st, (uint32_t)a.m, d);
+                vt[i] = fmaf(a.sigma[(a.sigma_per_step ? st * NU : 0) + d], z, a.nu[st * NU + d]);
+            }
+        }
+    }
+    // The rows of A x: x itself, its differences with the one and two steps
+    // before (across the groups' edge, values m1 and m2; 0 where the row is
+    // absent) and its prefix sums.  The sums run within a block of four, over
+    // the blocks and over the groups, so that no rounding chain is longer than
+    // a wave-wide scan's.
+    auto diff1 = [&](const float (&x)[R], int i, float m1) {
+        const float r = x[i] - (i >= 1 ? x[i >= 1 ? i - 1 : 0] : m1);
+        return (i >= 1 || h1) && present(i) ? r : 0.f;
+    };
+    auto diff2 = [&](const float (&x)[R], int i, float m1, float m2) {
+        const float b = i >= 1 ? x[i >= 1 ? i - 1 : 0] : m1;
+        const float c = i >= 2 ? x[i >= 2 ? i - 2 : 0] : (i == 1 ? m1 : m2);
+        const float r = (x[i] - 2.f * b) + c;
+        return (i >= 2 || h1) && present(i) ? r : 0.f;
+    };
+    // Sums over the blocks before this one (in the scan's direction): of this
+    // lane in double, of the groups before it likewise, handed back as a float
+    // and what it lacks.  A block's elements share this offset, so its
+    // rounding would move them together and the prefix-sum rows of all later
+    // steps with it; every other rounding of the scans is an element's own.
+    auto move = [&](int addr, double x, bool on) {
+        const int2 w = __builtin_bit_cast(int2, x);
+        const int2 m = {__builtin_amdgcn_ds_bpermute(addr, w.x), __builtin_amdgcn_ds_bpermute(addr, w.y)};
+        return on ? __builtin_bit_cast(double, m) : 0.0;
+    };
+    auto below = [&](double x) { return (move(dn3, x, h3) + move(dn2, x, h2)) + move(dn1, x, h1); };
+    auto above = [&](double x) { return (move(up3, x, g3) + move(up2, x, g2)) + move(up1, x, g1); };
+    auto hi_lo = [](double x, float &hi, float &lo) {
+        hi = (float)x;
+        lo = (float)(x - (double)hi);
+    };
+    auto prefix4 = [](const float *x, float *o) {
+        o[0] = x[0];
+        o[1] = x[0] + x[1];
+        o[2] = o[1] + x[2];
+        o[3] = o[1] + (x[2] + x[3]);
+    };
+    const float blo[3] = {-um, -da, -dj}, bhi[3] = {um, da, dj};
+    float tL[R];  // A v~, prefix-sum rows (the others follow from v~)
+    // (every lane takes part in the crossbar moves; the selects come after)
+    float tm1 = from(dn1, vt[R - 1]), tm2 = from(dn1, vt[R - 2]);
+    tm1 = h1 ? tm1 : 0.f;
+    tm2 = h1 ? tm2 : 0.f;
+    {
+        float o[R], hi[NB], lo[NB];
+        double t = 0.0, off[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            prefix4(vt + 4 * b, o + 4 * b);
+            off[b] = t;
+            t += (double)o[4 * b + 3];
+        }
+        const double g = below(t);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) hi_lo(off[b] + g, hi[b], lo[b]);
+#pragma unroll
+        for (int i = 0; i < R; ++i) tL[i] = present(i) ? hi[i >> 2] + (o[i] + lo[i >> 2]) : 0.f;
+    }
+    auto target = [&](int k, int i) { return k == 0 ? vt[i] : (k == 1 ? diff1(vt, i, tm1) : diff2(vt, i, tm1, tm2)); };
+    // State of row k (0 identity, 1, 2 differences) of step i.
+    // LEAN: the relaxed value s alone, of which z = clip(s) and w = s - z; else
+    // what the next iteration takes of them, g = (1 - alpha) z + w and
+    // y = z - w - A v~.
+    constexpr bool LEAN = NB > 4;
+    const float alpha = a.alpha, beta = 1.f - a.alpha;
+    float G[3][R], Y[3][LEAN ? 1 : R];
+    auto put = [&](int k, int i, float sv) {
+        if (LEAN) {
+            G[k][i] = sv;
+        } else {
+            const float z = __builtin_amdgcn_fmed3f(sv, blo[k], bhi[k]), w = sv - z;
+            G[k][i] = fmaf(beta, z, w);
+            Y[k][LEAN ? 0 : i] = (z - w) - target(k, i);
+        }
+    };
+    auto get_y = [&](int k, int i) {
+        if (!LEAN) return Y[k][LEAN ? 0 : i];
+        const float z = __builtin_amdgcn_fmed3f(G[k][i], blo[k], bhi[k]), w = G[k][i] - z;
+        return (z - w) - target(k, i);
+    };
+    auto relax = [&](int k, int i, float av) {
+        if (!LEAN) return fmaf(alpha, av, G[k][i]);
+        const float z = __builtin_amdgcn_fmed3f(G[k][i], blo[k], bhi[k]), w = G[k][i] - z;
+        return fmaf(alpha, av, fmaf(beta, z, w));
+    };
+    // The prefix-sum rows run to a hundred times the others' size, so they keep
+    // z and w themselves: w += a - z then carries the rounding of a + w, which
+    // s - z would lose.  Absent ones stay at z = w = 0.
+    float zL[R], wL[R];
+    auto get_yL = [&](int i) { return (zL[i] - wL[i]) - tL[i]; };
+    float v[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        v[i] = vt[i];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) put(k, i, __builtin_amdgcn_fmed3f(target(k, i), blo[k], bhi[k]));  // z = clip(A v~), w = 0
+        zL[i] = present(i) ? __builtin_amdgcn_fmed3f(tL[i], loL, hiL) : 0.f;
+        wL[i] = 0.f;
+    }
+    int p_off = lane;
+    for (int it = 0; it < a.iters; ++it) {
+        // P's operands are read from LDS in every iteration (hoisted out of the
+        // loop they would take up to 384 registers)
+        asm volatile("" : "+v"(p_off));
+        const h8 *P8 = reinterpret_cast<const h8 *>(PA) + p_off;
+        // right-hand side A^T (z - w - A v~), from the last step down
+        float r[R];
+        {
+            double t = 0.0, off[NB];
+            float hi[NB], lo[NB];
+#pragma unroll
+            for (int b = NB - 1; b >= 0; --b) {
+                const float x[4] = {get_yL(4 * b + 3), get_yL(4 * b + 2), get_yL(4 * b + 1), get_yL(4 * b)};
+                float o[4];
+                prefix4(x, o);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) r[4 * b + 3 - c] = o[c];
+                off[b] = t;
+                t += (double)o[3];
+            }
+            float y1n = from(up1, get_y(1, 0)), y2n = from(up1, get_y(2, 0)), y2nn = from(up1, get_y(2, 1));
+            const double g = above(t);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) hi_lo(off[b] + g, hi[b], lo[b]);
+            y1n = g1 ? y1n : 0.f;
+            y2n = g1 ? y2n : 0.f;
+            y2nn = g1 ? y2nn : 0.f;
+#pragma unroll
+            for (int i = R - 1; i >= 0; --i) {
+                const float y1 = get_y(1, i), y2 = get_y(2, i);
+                r[i] = get_y(0, i) + (y1 - y1n) + ((y2 - 2.f * y2n) + y2nn) + (hi[i >> 2] + (r[i] + lo[i >> 2]));
+                y1n = y1;
+                y2nn = y2n;
+                y2n = y2;
+            }
+        }
+        // The product, one row block after another, and the rows of A v with
+        // the relaxed update, each piece of a block between the MFMAs of the
+        // next block (the scheduling fences keep it there): one wave per SIMD
+        // has nothing else to run under them.  What waits for the other groups
+        // (the first two steps' differences, the prefix sums) comes last.
+        // the parts of the right-hand side as MFMA operands, eight steps each
+        union Op {
+            uint32_t u[4];
+            h8 h;
+        } rp[KS][3];
+#pragma unroll
+        for (int i = 0; i < 8 * KS; i += 2) {
+            uint32_t x[3] = {0u, 0u, 0u};
+            if (i < R) split3(r[i < R ? i : 0], r[i < R ? i + 1 : 0], x);
+#pragma unroll
+            for (int t = 0; t < 3; ++t) rp[i >> 3][t].u[(i & 7) >> 1] = x[t];
+        }
+        f4 acc[NB];
+        auto piece = [&](int p) {  // row kind p % 4 of step p / 4 (0: the step itself)
+            const int i = p >> 2;
+            if ((p & 3) == 0) v[i] = vt[i] + acc[i >> 2][i & 3];
+            if ((p & 3) == 1) put(0, i, relax(0, i, v[i]));
+            if ((p & 3) == 2 && i >= 1) put(1, i, relax(1, i, diff1(v, i, 0.f)));
+            if ((p & 3) == 3 && i >= 2) put(2, i, relax(2, i, diff2(v, i, 0.f, 0.f)));
+        };
+        constexpr int PP = (16 + 6 * KS - 1) / (6 * KS);  // pieces between two MFMAs
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            acc[b] = f4{0.f, 0.f, 0.f, 0.f};
+            h8 pa[KS][3];
+#pragma unroll
+            for (int k = 0; k < KS; ++k)
+#pragma unroll
+                for (int t = 0; t < 3; ++t) pa[k][t] = P8[64 * ((b * KS + k) * 3 + t)];
+            // the six leading products of the parts, small ones first
+            constexpr int TP[6] = {0, 2, 1, 0, 1, 0}, TR[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+            for (int e = 0; e < 6 * KS; ++e) {
+                acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa[e % KS][TP[e / KS]], rp[e % KS][TR[e / KS]].h, acc[b], 0, 0, 0);
+                if (b > 0) {
+#pragma unroll
+                    for (int p = PP * e; p < PP * (e + 1); ++p)
+                        if (p < 16) piece(16 * (b - 1) + p);
+                    if (PP * e < 16) __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+#pragma unroll
+        for (int n = 0; n < 16; ++n) piece(16 * (NB - 1) + n);
+        float o[R], hi[NB], lo[NB];
+        double t = 0.0, off[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            prefix4(v + 4 * b, o + 4 * b);
+            off[b] = t;
+            t += (double)o[4 * b + 3];
+        }
+        float m1 = from(dn1, v[R - 1]), m2 = from(dn1, v[R - 2]);
+        const double g = below(t);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) hi_lo(off[b] + g, hi[b], lo[b]);
+        m1 = h1 ? m1 : 0.f;
+        m2 = h1 ? m2 : 0.f;
+        put(1, 0, relax(1, 0, diff1(v, 0, m1)));
+        put(2, 0, relax(2, 0, diff2(v, 0, m1, m2)));
+        put(2, 1, relax(2, 1, diff2(v, 1, m1, m2)));
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const float av = fmaf(alpha, hi[i >> 2] + (o[i] + lo[i >> 2]), beta * zL[i]);
+            const float z = __builtin_amdgcn_fmed3f(av + wL[i], loL, hiL);
+            wL[i] = present(i) ? wL[i] + (av - z) : 0.f;
+            zL[i] = present(i) ? z : 0.f;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+        if (live && present(i)) a.U_out[((long)j * H + s0 + i) * NU + d] = clipf(v[i], -um, um);
+}
+
+template <int NB>
+static void launch_tile(const ProjectArgs &a, hipStream_t s)
+{
+    const unsigned grid = (unsigned)(((long)a.K * NU + 63) / 64);
+    const size_t lds = (size_t)NB * ((4 * NB + 7) / 8) * 3 * 64 * 16;
+    if (a.H == 16 * NB)
+        hipLaunchKernelGGL((project_tile_kernel<NB, true>), dim3(grid), dim3(256), lds, s, a);
+    else
+        hipLaunchKernelGGL((project_tile_kernel<NB, false>), dim3(grid), dim3(256), lds, s, a);
+}
+
+// The workgroup-per-sample form takes about 66 us (H <= 64) or 150 us (beyond)
+// for every 256 samples, one workgroup a CU; the tile form 69, 130, 285 and
+// 318 us at H = 24, 64, 100 and 128 for up to 1170 samples (a wave a SIMD) and
+// as much again for the next.  So the tile form is taken from the sample count
+// on at which it is the faster: 257 samples up to H = 32, 513 beyond
+// (K = 513..768: 198 against 130 us at H = 64, 443 against 318 at H = 128).
+// Up to H = 16 the other form's FP32 product is the more exact one (2.1e-6
+// against 2.6e-6 of the result's norm at H = 8), and stays.
 void launch_project(const ProjectArgs &a, hipStream_t s)
 {
+    if (a.H > 16 && a.K > (a.H <= 32 ? 256 : 512)) {
+        switch ((a.H + 15) / 16) {
+        case 2: return launch_tile<2>(a, s);
+        case 3: return launch_tile<3>(a, s);
+        case 4: return launch_tile<4>(a, s);
+        case 5: return launch_tile<5>(a, s);
+        case 6: return launch_tile<6>(a, s);
+        case 7: return launch_tile<7>(a, s);
+        default: return launch_tile<8>(a, s);
+        }
+    }
     if (a.H <= 64) {
         if (a.H == 64)
             hipLaunchKernelGGL((project_kernel<1, true>), dim3(a.K), dim3(14 * 64), 0, s, a);
