@@ -695,9 +695,9 @@ static int plan_impl(mppi_ctx *ctx, const mppi_scene *scene, const float *x0, co
     if (cov) {
         const size_t nn = (size_t)n * n;
         if ((rc = ensure(ctx, S_COVS, nn * sizeof(double), &dS)) || (rc = ensure(ctx, S_COVA, nn * sizeof(double), &dA)) ||
-            (rc = ensure(ctx, S_COVL, nn * sizeof(double), &dL)) || (rc = ensure(ctx, S_COVL32, nn * sizeof(float), &dL32)) ||
+            (rc = ensure(ctx, S_COVL, nn * sizeof(double), &dL)) || (rc = ensure(ctx, S_COVL32, sample_l_bytes(n), &dL32)) ||
             (rc = ensure(ctx, S_COVLI, 2 * 32 * 32 * sizeof(double) + 256, &dLi)) ||
-            (rc = ensure(ctx, S_COVZ, (size_t)K * n * sizeof(float), &dZ)) ||
+            (rc = ensure(ctx, S_COVZ, sample_z_bytes(K, n), &dZ)) ||
             (rc = ensure(ctx, S_COVU, (size_t)K * n * sizeof(float), &dUc)) ||
             (rc = ensure(ctx, S_NU64, (size_t)n * sizeof(double), &dnu64)))
             return rc;
@@ -756,11 +756,11 @@ static int plan_impl(mppi_ctx *ctx, const mppi_scene *scene, const float *x0, co
             const float *Ucur = nullptr;
             if (cov) {
                 // factor Sigma_m, then draw clip(nu_m + L_m z_j) for every sample
-                CholArgs ca = {(const double *)dS, (double *)dA, (double *)dL, (float *)dL32, (double *)dLi, dflag,
+                CholArgs ca = {(const double *)dS, (double *)dA, (double *)dL, (double *)dLi, dflag,
                                n, m == 0 ? 1 : 0};
                 launch_cholesky(ca, q);
-                SampleFullArgs sf = {(float *)dZ, (const float *)dL32, (const float *)dnu, (float *)dUc, K, n, k0, k1,
-                                     m, scene->host.u_max};
+                SampleFullArgs sf = {(unsigned short *)dZ, (unsigned short *)dL32, (const double *)dL,
+                                     (const float *)dnu, (float *)dUc, K, n, k0, k1, m, scene->host.u_max};
                 launch_sample_full(sf, q);
                 Ucur = (const float *)dUc;
                 ra.U = Ucur;
@@ -1126,7 +1126,7 @@ int mppi_cholesky(mppi_ctx *ctx, const double *Sigma, double *L, int n, unsigned
         return rc;
     if ((rc = out_ptr(ctx, S_COVL, L, nn * sizeof(double), dev, &dL))) return rc;
     int *dflag = (int *)((char *)dLi + 2 * 32 * 32 * sizeof(double));
-    CholArgs ca = {(const double *)dS, (double *)dA, (double *)dL, nullptr, (double *)dLi, dflag, n, 1};
+    CholArgs ca = {(const double *)dS, (double *)dA, (double *)dL, (double *)dLi, dflag, n, 1};
     launch_cholesky(ca, s);
     HIPCHK(hipGetLastError());
     if ((rc = copy_out(L, dL, nn * sizeof(double), dev, s))) return rc;
@@ -1158,14 +1158,12 @@ int mppi_sample_full(mppi_ctx *ctx, const float *nu, const double *L, uint64_t s
         (rc = stage_in(ctx, S_COVL, L, nn * sizeof(double), dev, s, &dL)))
         return rc;
     void *dL32, *dZ, *dout;
-    if ((rc = ensure(ctx, S_COVL32, nn * sizeof(float), &dL32)) ||
-        (rc = ensure(ctx, S_COVZ, (size_t)K * n * sizeof(float), &dZ)))
+    if ((rc = ensure(ctx, S_COVL32, sample_l_bytes(n), &dL32)) ||
+        (rc = ensure(ctx, S_COVZ, sample_z_bytes(K, n), &dZ)))
         return rc;
     if ((rc = out_ptr(ctx, S_COVU, U, (size_t)K * n * sizeof(float), dev, &dout))) return rc;
-    // the upper triangle of L is not read: it becomes zero in the single-precision copy
-    launch_to_f32((const double *)dL, (float *)dL32, (long)nn, s);
-    launch_lower_f32((float *)dL32, n, s);
-    SampleFullArgs sf = {(float *)dZ, (const float *)dL32, (const float *)dnu, (float *)dout, K, n,
+    SampleFullArgs sf = {(unsigned short *)dZ, (unsigned short *)dL32, (const double *)dL, (const float *)dnu,
+                         (float *)dout, K, n,
                          (uint32_t)(seed & 0xffffffffu), (uint32_t)(seed >> 32), m, u_max};
     launch_sample_full(sf, s);
     HIPCHK(hipGetLastError());

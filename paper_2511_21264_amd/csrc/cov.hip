@@ -16,9 +16,9 @@
 //                      (FP64 MFMA); the tile (r, r) also stores its panel block
 //                      as the factor, and the workgroup of the next diagonal
 //                      tile factors and inverts it in registers once updated
-//   sample_full_kernel U = clip(nu + Z L^T, +-u_max): FP32 MFMA 16x16x4 over
-//                      16 x 64 tiles staged through LDS in 32-wide chunks,
-//                      skipping the zero upper triangle of L
+//   sample_*_kernel    U = clip(nu + Z L^T, +-u_max): both factors as three
+//                      bf16 parts in operand order, bf16 MFMA 16x16x32 over
+//                      32 x 64 tiles, skipping the zero upper triangle of L
 //
 // MFMA 16x16x4 operand layout: lane l supplies A[l % 16][l / 16] and
 // B[l / 16][l % 16]; result element v of lane l is D[4 (l / 16) + v][l % 16]
@@ -186,7 +186,6 @@ __global__ void __launch_bounds__(256) chol_init_kernel(CholArgs a)
             a.A[e] = a.S[e];
         } else {
             a.L[e] = 0.0;
-            if (a.L32) a.L32[e] = 0.f;
         }
     }
     if (a.reset_flag && blockIdx.x == 0 && threadIdx.x == 0) *a.flag = a.n;
@@ -201,7 +200,7 @@ __device__ __forceinline__ double pick4(const double v[4], int i)
 
 // Factor the diagonal block held in s (lower triangle valid for rows and
 // columns < nbk), invert it, and store the factor block of columns c0.. into
-// L (and L32) and the inverse into Linv.  256 threads: thread t keeps the
+// L and the inverse into Linv.  256 threads: thread t keeps the
 // entries (t / 32 + 8 k, t % 32), k = 0..3, of the block and of its inverse
 // in registers.  Columns go four at a time: their owners publish them (and
 // the four matching rows of the inverse) to LDS, one barrier, then every
@@ -309,7 +308,6 @@ __device__ void factor_block(const double (*s)[CB + 1], double (*cbuf)[4][CB], d
         if (r < nbk && q <= r) {
             const long e = (long)(c0b + r) * n + c0b + q;
             a.L[e] = sv[k];
-            if (a.L32) a.L32[e] = (float)sv[k];
         }
     }
 }
@@ -394,7 +392,6 @@ __global__ void __launch_bounds__(256) chol_step_kernel(CholArgs a, int b)
             if (R0 + x >= n) continue;
             const long eL = (long)(R0 + x) * n + c0 + y;
             a.L[eL] = pr[x][y];
-            if (a.L32) a.L32[eL] = (float)pr[x][y];
         }
     }
     if (next) {
@@ -417,78 +414,174 @@ void launch_cholesky(const CholArgs &a, hipStream_t s)
 }
 
 // ------------------------------------------------------------------ sampling
-__global__ void __launch_bounds__(256) normals_kernel(SampleFullArgs a)
+// U = clip(nu + Z L^T) with Z (K x n normals) and L (n x n, lower) split into
+// three bf16 parts each (24 bits and more; L's from double), the product as
+// six bf16 partial products accumulated in FP32: 2.7 times the FP32 matrix
+// rate, and closer to FP64 than with L rounded to FP32 (2.7e-7 of the result's
+// norm against 3.2e-7).  Two launches instead of four (conversion of L,
+// clearing of its upper triangle, normals, product): K = 1024, n = 896 39.8 ->
+// 24.6 us, K = 4096, n = 1400 184 -> 99 us; what is left is the operands' way
+// from the L2 (three chunks ahead; one ahead 29.9 us), not the products' 2 us.
+//
+// Both are laid out as MFMA 16x16x32 operands: 16 rows x 32 columns are 64
+// lanes x 8 values (lane l: row l % 16, columns 8 (l / 16) ..), part after
+// part, so a wave reads an operand as one contiguous kilobyte.  Rows past K or
+// n and columns past n are zero; of L only the chunks up to the diagonal exist.
+typedef __bf16 b8 __attribute__((ext_vector_type(8)));
+
+__device__ __forceinline__ void split3(float x, unsigned short p[3])
 {
-    const long n = a.n, N = (long)a.K * n;
-    for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < N; e += (long)gridDim.x * blockDim.x) {
-        const long j = e / n;
-        const int i = (int)(e - j * n);
-        a.Z[e] = normal_joint(a.key0, a.key1, (uint32_t)j, (uint32_t)(i / NU), (uint32_t)a.m, i % NU);
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+        const __bf16 b = (__bf16)x;
+        p[t] = __builtin_bit_cast(unsigned short, b);
+        x -= (float)b;
     }
 }
 
-// output tile: 16 samples (j) x 64 sequence entries (i); wave w owns entries
-// i0 + 16 w .. + 15 (one 16x16 MFMA block); the sum over p runs in chunks of
-// 32 columns staged through LDS.  Small tiles keep several workgroups per
-// CU, whose loads overlap.
-constexpr int SJ = 16, SI = 64, SP = 32;
+struct Parts8 {
+    unsigned short v[3][8];
+};
+__device__ __forceinline__ void put_parts(unsigned short *dst, const Parts8 &q)
+{
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+        uint4 w;
+        __builtin_memcpy(&w, q.v[t], 16);
+        *reinterpret_cast<uint4 *>(dst + 512 * t) = w;  // 64 lanes x 8 to the next part
+    }
+}
+
+// Operands of the product.  The first nzb workgroups write Z: a thread takes
+// one sample's eight columns, the 64 lanes of a wave 64 samples of the same
+// columns, so that the walk over the counters (a Philox call a quarter step,
+// a Box-Muller pair every other column) is uniform; drawn a normal at a time
+// as before, every value repeated both.  The others write L: a thread takes
+// eight columns of a row.
+__global__ void __launch_bounds__(256) sample_operands_kernel(SampleFullArgs a, int nzb)
+{
+    const int n = a.n, K = a.K, nc = (n + 31) >> 5;  // chunks of 32 columns
+    if ((int)blockIdx.x < nzb) {
+        const int w = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+        const int oc = 4 * nc, jb = w / oc, o = w - jb * oc;  // 64 samples, 8 columns
+        const int j = 64 * jb + lane;
+        if (64 * jb >= K) return;
+        Parts8 q = {};
+        U4 rnd = {};
+        float z0 = 0.f, z1 = 0.f;
+        int have = -1;  // quarter step of rnd
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int p = __builtin_amdgcn_readfirstlane(8 * o + e);
+            if (p < n) {
+                const int k = p / NU, d = p - k * NU, quarter = 4 * k + (d >> 2);
+                if (quarter != have) {
+                    rnd = philox4x32_10(U4{(uint32_t)j, (uint32_t)k, (uint32_t)(d >> 2), (uint32_t)a.m}, a.key0, a.key1);
+                    have = quarter;
+                }
+                if (e == 0 || (d & 1) == 0) {
+                    const bool hi = (d & 3) >> 1;
+                    box_muller(hi ? rnd.z : rnd.x, hi ? rnd.w : rnd.y, z0, z1);
+                }
+                unsigned short t[3];
+                split3((d & 1) ? z1 : z0, t);
+                q.v[0][e] = t[0]; q.v[1][e] = t[1]; q.v[2][e] = t[2];
+            }
+        }
+        if (j >= K) q = Parts8{};
+        const int c = o >> 2, l = 16 * (o & 3) + (j & 15);
+        put_parts(a.Z + (((long)(j >> 4) * nc + c) * 192 + l) * 8, q);
+        return;
+    }
+    const int nt = (n + 15) >> 4;
+    const long w = (long)(blockIdx.x - nzb) * 4 + (threadIdx.x >> 6);
+    const int ib = (int)(w / nc), c = (int)(w - (long)ib * nc), lane = threadIdx.x & 63;
+    if (ib >= nt || 32 * c > 16 * ib + 15) return;
+    const int i = 16 * ib + (lane & 15), p0 = 32 * c + 8 * (lane >> 4);
+    Parts8 q = {};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int p = p0 + e;
+        if (i < n && p <= i) {
+            double x = a.L[(long)i * n + p];
+#pragma unroll
+            for (int t = 0; t < 3; ++t) {
+                const __bf16 b = (__bf16)(float)x;
+                q.v[t][e] = __builtin_bit_cast(unsigned short, b);
+                x -= (double)(float)b;
+            }
+        }
+    }
+    put_parts(a.Lp + (((long)ib * nc + c) * 192 + lane) * 8, q);
+}
+
+// Output tile: 32 samples x 64 entries; wave w owns entries i0 + 16 w .. + 15
+// (two 16x16 results).  Operands go straight to registers, SD chunks ahead of
+// their products: no LDS, no barrier.  Tiles of the last
+// entries, whose sums are the longest, are handed out first; consecutive
+// workgroups take different samples, so that with a multiple of eight sample
+// tiles an XCD keeps to its own.
+constexpr int SJ = 32, SI = 64, SD = 3;
 
 __global__ void __launch_bounds__(256) sample_full_kernel(SampleFullArgs a)
 {
-    __shared__ float zs[SJ][SP + 1];
-    __shared__ float ls[SI][SP + 1];
-    const int n = a.n, K = a.K;
-    // all column tiles of a block of samples on one XCD (their normals share its L2)
-    const int ni = (n + SI - 1) / SI, tile = xcd_order(blockIdx.x, gridDim.x);
-    const int i0 = (tile % ni) * SI, j0 = (tile / ni) * SJ;
-    const int t = threadIdx.x, wv = t >> 6, lane = t & 63, r = lane & 15, q = lane >> 4;
-    f4 c0 = {0.f, 0.f, 0.f, 0.f};
-    const int pend = min(n, i0 + SI);  // L is lower: columns past the tile's last row are zero
-    // chunk p0 holds Z[j0.., p0..] (16 x 32) and L[i0.., p0..] (64 x 32):
-    // thread t takes column t % 32; the next chunk is loaded into registers
-    // while the current one is multiplied
-    const int pc = t & 31, rw = t >> 5;
-    float zr[SJ / 8], lr[SI / 8];
-    auto load = [&](int p0) {
-        const int p = p0 + pc;
+    const int n = a.n, K = a.K, nc = (n + 31) >> 5;
+    const int nj = (K + SJ - 1) / SJ, ni = (n + SI - 1) / SI;
+    const int it = ni - 1 - (int)(blockIdx.x / nj), jt = blockIdx.x % nj;
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
+    const int ib = 4 * it + wv, j0 = SJ * jt;
+    if (16 * ib >= n) return;
+    const int nch = ((16 * ib + 15) >> 5) + 1;  // chunks up to the diagonal
+    const bool two = j0 + 16 < K;               // the second sample block holds a sample
+    const b8 *z0 = reinterpret_cast<const b8 *>(a.Z) + (long)(2 * jt) * nc * 192 + lane;
+    const b8 *z1 = z0 + (two ? (long)nc * 192 : 0);
+    const b8 *lp = reinterpret_cast<const b8 *>(a.Lp) + (long)ib * nc * 192 + lane;
+    f4 c0 = {0.f, 0.f, 0.f, 0.f}, c1 = c0;
+    b8 x0[SD][3], x1[SD][3], y[SD][3];
+    auto load = [&](int s, int c) {
 #pragma unroll
-        for (int u = 0; u < SJ / 8; ++u) {
-            const int row = rw + 8 * u;
-            zr[u] = (j0 + row < K && p < n) ? a.Z[(long)(j0 + row) * n + p] : 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < SI / 8; ++u) {
-            const int row = rw + 8 * u;
-            lr[u] = (i0 + row < n && p < n) ? a.L32[(long)(i0 + row) * n + p] : 0.f;
+        for (int t = 0; t < 3; ++t) {
+            y[s][t] = lp[192 * c + 64 * t];
+            x0[s][t] = z0[192 * c + 64 * t];
+            x1[s][t] = z1[192 * c + 64 * t];
         }
     };
-    load(0);
-    for (int p0 = 0; p0 < pend; p0 += SP) {
 #pragma unroll
-        for (int u = 0; u < SJ / 8; ++u) zs[rw + 8 * u][pc] = zr[u];
+    for (int s = 0; s < SD; ++s) load(s, min(s, nch - 1));
+    for (int cb = 0; cb < nch; cb += SD) {
 #pragma unroll
-        for (int u = 0; u < SI / 8; ++u) ls[rw + 8 * u][pc] = lr[u];
-        __syncthreads();
-        if (p0 + SP < pend) load(p0 + SP);
+        for (int s = 0; s < SD; ++s) {
+            if (cb + s < nch) {  // uniform over the wave
+                constexpr int TX[6] = {0, 2, 1, 0, 1, 0}, TY[6] = {2, 0, 1, 1, 0, 0};  // small products first
 #pragma unroll
-        for (int kk = 0; kk < SP / 4; ++kk)
-            c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(zs[r][4 * kk + q], ls[16 * wv + r][4 * kk + q], c0, 0, 0, 0);
-        __syncthreads();
+                for (int e = 0; e < 6; ++e) {
+                    c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x0[s][TX[e]], y[s][TY[e]], c0, 0, 0, 0);
+                    c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x1[s][TX[e]], y[s][TY[e]], c1, 0, 0, 0);
+                }
+                load(s, min(cb + s + SD, nch - 1));
+            }
+        }
     }
-    const int ib = i0 + 16 * wv + r;
-    const float nui = ib < n ? a.nu[ib] : 0.f;
+    const int i = 16 * ib + r;
+    if (i >= n) return;
+    const float nui = a.nu[i];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const int ja = j0 + 4 * q + v;
-        if (ja < K && ib < n) a.U[(long)ja * n + ib] = fminf(fmaxf(nui + c0[v], -a.u_max), a.u_max);
+    for (int e = 0; e < 4; ++e) {
+        const int ja = j0 + 4 * q + e;
+        if (ja < K) a.U[(long)ja * n + i] = fminf(fmaxf(nui + c0[e], -a.u_max), a.u_max);
+        if (ja + 16 < K) a.U[(long)(ja + 16) * n + i] = fminf(fmaxf(nui + c1[e], -a.u_max), a.u_max);
     }
 }
 
+size_t sample_z_bytes(int K, int n) { return (size_t)((K + 63) / 64) * 4 * ((n + 31) / 32) * 192 * 16; }
+size_t sample_l_bytes(int n) { return (size_t)((n + 15) / 16) * ((n + 31) / 32) * 192 * 16; }
+
 void launch_sample_full(const SampleFullArgs &a, hipStream_t s)
 {
-    const long N = (long)a.K * a.n;
-    const int g = (int)std::min<long>((N + 255) / 256, 8192);
-    hipLaunchKernelGGL(normals_kernel, dim3(g), dim3(256), 0, s, a);
+    const int nc = (a.n + 31) / 32, nt = (a.n + 15) / 16;
+    const int nzb = (a.K + 63) / 64 * nc;  // four waves of (64 samples, 8 columns) a workgroup
+    const int nlb = (nt * nc + 3) / 4;
+    hipLaunchKernelGGL(sample_operands_kernel, dim3(nzb + nlb), dim3(256), 0, s, a, nzb);
     hipLaunchKernelGGL(sample_full_kernel, dim3(((a.n + SI - 1) / SI) * ((a.K + SJ - 1) / SJ)), dim3(256), 0, s, a);
 }
 
@@ -511,34 +604,6 @@ void launch_diag_sigma(const float *sigma, int sps, int n, double *S, hipStream_
     const long N = (long)n * n;
     const int g = (int)std::min<long>((N + 255) / 256, 4096);
     hipLaunchKernelGGL(diag_sigma_kernel, dim3(g), dim3(256), 0, s, sigma, sps, n, S);
-}
-
-__global__ void __launch_bounds__(256) to_f32_kernel(const double *src, float *dst, long N)
-{
-    for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < N; e += (long)gridDim.x * blockDim.x)
-        dst[e] = (float)src[e];
-}
-
-void launch_to_f32(const double *src, float *dst, long N, hipStream_t s)
-{
-    const int g = (int)std::min<long>((N + 255) / 256, 4096);
-    hipLaunchKernelGGL(to_f32_kernel, dim3(g), dim3(256), 0, s, src, dst, N);
-}
-
-__global__ void __launch_bounds__(256) lower_f32_kernel(float *L, int n)
-{
-    const long N = (long)n * n;
-    for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < N; e += (long)gridDim.x * blockDim.x) {
-        const long i = e / n, l = e - i * n;
-        if (l > i) L[e] = 0.f;
-    }
-}
-
-void launch_lower_f32(float *L, int n, hipStream_t s)
-{
-    const long N = (long)n * n;
-    const int g = (int)std::min<long>((N + 255) / 256, 4096);
-    hipLaunchKernelGGL(lower_f32_kernel, dim3(g), dim3(256), 0, s, L, n);
 }
 
 }  // namespace mppi

@@ -141,7 +141,6 @@ struct CholArgs {
     const double *S;  // [n][n] (lower triangle read)
     double *A;        // [n][n] work copy (lower), updated in place
     double *L;        // [n][n] factor (upper triangle zeroed); may be S
-    float *L32;       // [n][n] the factor in single precision (nullable)
     double *Linv;     // [2][32][32] inverses of the diagonal blocks (block b in half b & 1)
     int *flag;        // first column with a non-positive pivot, n if none
     int n;
@@ -150,8 +149,9 @@ struct CholArgs {
 void launch_cholesky(const CholArgs &a, hipStream_t s);
 
 struct SampleFullArgs {
-    float *Z;           // [K][n] scratch: the Philox normals of iteration m
-    const float *L32;   // [n][n] lower factor, upper triangle zero
+    unsigned short *Z;  // scratch of sample_z_bytes: the Philox normals of iteration m in bf16 parts
+    unsigned short *Lp; // scratch of sample_l_bytes: the factor in bf16 parts
+    const double *L;    // [n][n] factor (lower triangle read)
     const float *nu;    // [n] mean
     float *U;           // [K][n] clip(nu + L z_j)
     int K, n;
@@ -160,10 +160,10 @@ struct SampleFullArgs {
     float u_max;
 };
 void launch_sample_full(const SampleFullArgs &a, hipStream_t s);
+size_t sample_z_bytes(int K, int n);
+size_t sample_l_bytes(int n);
 // Sigma = diag(sigma^2) over n = 14 H (sigma[14] or [H][14])
 void launch_diag_sigma(const float *sigma, int sps, int n, double *S, hipStream_t s);
-void launch_to_f32(const double *src, float *dst, long n, hipStream_t s);
-void launch_lower_f32(float *L, int n, hipStream_t s);  // zero the upper triangle
 
 // The best sample's sequence of an iteration (Alg. 1 returns the lowest-cost
 // sequence of the final iteration): row st->best of the stored samples, or
