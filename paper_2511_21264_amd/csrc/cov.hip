@@ -70,48 +70,55 @@ __device__ __forceinline__ double wave_sum_f64(double x)
 // ------------------------------------------------------------ covariance update
 constexpr int CG = 8;  // groups of four samples per wave and step
 
-__global__ void __launch_bounds__(256) cov_syrk_kernel(CovArgs a)
+// CW: waves per tile.  Bound by issue: per group of four samples a wave's four
+// FP64 MFMAs (64 cycles each) and its vector instructions, which run one after
+// the other.  So indices past K or n are clamped instead of tested (their
+// columns are not stored, their weight is 0) and offsets are 32-bit where they
+// fit.  K = 1024, n = 896: 40.3 -> 37.4 us; K = 4096, n = 1400: 268 -> 233 us
+// (17 TFLOP/s of the lower triangle).  What is left at n = 896 is the tail: 406 tiles on
+// 256 CUs, so some CUs have two.
+template <int CW, typename Off>
+__global__ void __launch_bounds__(64 * CW) cov_syrk_kernel(CovArgs a)
 {
-    __shared__ double red[4][CT][CT + 1];
-    __shared__ double wred[4];
+    __shared__ double red[CW][CT][CT + 1];
+    __shared__ double wred[CW];
     int bi, bl;
     tri_index(xcd_order(blockIdx.x, gridDim.x), bi, bl);  // consecutive rows of tiles share an XCD
     const int n = a.n, K = a.K;
     const int i0 = bi * CT, l0 = bl * CT;
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int r = lane & 15, q = lane >> 4;
-    const int ia0 = i0 + r, ia1 = ia0 + 16, lb0 = l0 + r, lb1 = lb0 + 16;
-    const double na0 = ia0 < n ? a.nu[ia0] : 0.0, na1 = ia1 < n ? a.nu[ia1] : 0.0;
-    const double nl0 = lb0 < n ? a.nu[lb0] : 0.0, nl1 = lb1 < n ? a.nu[lb1] : 0.0;
+    const int ia0 = min(i0 + r, n - 1), ia1 = min(i0 + r + 16, n - 1), lb0 = min(l0 + r, n - 1), lb1 = min(l0 + r + 16, n - 1);
+    const double na0 = a.nu[ia0], na1 = a.nu[ia1], nl0 = a.nu[lb0], nl1 = a.nu[lb1];
     d4 c00 = {0.0, 0.0, 0.0, 0.0}, c01 = c00, c10 = c00, c11 = c00;
     double ws = 0.0;
-    // wave wv takes the groups of four samples j0 = 4 wv, 4 wv + 16, ...,
+    // wave wv takes the groups of four samples j0 = 4 wv, 4 wv + 4 CW, ...,
     // CG groups per step; the loads of step s + 1 are issued before the
     // products of step s.  Sample values do not wait on their weight: a
-    // weightless sample is dropped by a select afterwards (so a non-finite
+    // weightless sample's are dropped by a select afterwards (so a non-finite
     // entry in it still contributes nothing).
     float uc[CG][4], un[CG][4] = {};
     double wc[CG], wn[CG] = {};
     auto load = [&](int j0, float (&u4)[CG][4], double (&w2)[CG]) {
 #pragma unroll
         for (int g = 0; g < CG; ++g) {
-            const int j = j0 + 16 * g + q;
-            const bool ok = j < K;
-            const float *u = a.U + (long)(ok ? j : 0) * n;
-            w2[g] = ok ? a.w[j] : 0.0;
-            u4[g][0] = (ok && ia0 < n) ? u[ia0] : 0.f;
-            u4[g][1] = (ok && ia1 < n) ? u[ia1] : 0.f;
-            u4[g][2] = (ok && lb0 < n) ? u[lb0] : 0.f;
-            u4[g][3] = (ok && lb1 < n) ? u[lb1] : 0.f;
+            const int j = j0 + 4 * CW * g + q, jc = min(j, K - 1);
+            const double w = a.w[jc];
+            w2[g] = j < K ? w : 0.0;
+            const Off o = (Off)jc * (Off)n;
+            u4[g][0] = a.U[o + (Off)ia0];
+            u4[g][1] = a.U[o + (Off)ia1];
+            u4[g][2] = a.U[o + (Off)lb0];
+            u4[g][3] = a.U[o + (Off)lb1];
         }
     };
     load(4 * wv, uc, wc);
-    for (int j0 = 4 * wv; j0 < K; j0 += 16 * CG) {
-        if (j0 + 16 * CG < K) load(j0 + 16 * CG, un, wn);
+    for (int j0 = 4 * wv; j0 < K; j0 += 4 * CW * CG) {
+        if (j0 + 4 * CW * CG < K) load(j0 + 4 * CW * CG, un, wn);
         bool any = false;
 #pragma unroll
         for (int g = 0; g < CG; ++g) {
-            if (r == 0) ws += wc[g];
+            ws += wc[g];  // on each of the 16 lanes that share the sample
             any = any || wc[g] != 0.0;
         }
         if (__ballot(any) != 0) {  // skipped when no group of the step carries weight
@@ -134,6 +141,7 @@ __global__ void __launch_bounds__(256) cov_syrk_kernel(CovArgs a)
             for (int e = 0; e < 4; ++e) uc[g][e] = un[g][e];
         }
     }
+    if (r != 0) ws = 0.0;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         red[wv][q + 4 * v][r] = c00[v];
@@ -144,12 +152,16 @@ __global__ void __launch_bounds__(256) cov_syrk_kernel(CovArgs a)
     ws = wave_sum_f64(ws);
     if (lane == 0) wred[wv] = ws;
     __syncthreads();
-    const double wsum = ((wred[0] + wred[1]) + wred[2]) + wred[3];
-    for (int e = threadIdx.x; e < CT * CT; e += 256) {
+    double wsum = wred[0];
+#pragma unroll
+    for (int w = 1; w < CW; ++w) wsum += wred[w];
+    for (int e = threadIdx.x; e < CT * CT; e += 64 * CW) {
         const int ti = e / CT, tl = e % CT;
         const int i = i0 + ti, l = l0 + tl;
         if (i >= n || l >= n || (bi == bl && ti < tl)) continue;
-        const double g = ((red[0][ti][tl] + red[1][ti][tl]) + red[2][ti][tl]) + red[3][ti][tl];
+        double g = red[0][ti][tl];
+#pragma unroll
+        for (int w = 1; w < CW; ++w) g += red[w][ti][tl];
         const double s_old = a.S_in[(long)i * n + l];
         // no weight at all (no finite cost): Sigma is kept, as the mean is
         double v = s_old;
@@ -162,7 +174,7 @@ __global__ void __launch_bounds__(256) cov_syrk_kernel(CovArgs a)
     }
     __syncthreads();
     // the mirrored upper half, written along its rows
-    for (int e = threadIdx.x; e < CT * CT; e += 256) {
+    for (int e = threadIdx.x; e < CT * CT; e += 64 * CW) {
         const int tl = e / CT, ti = e % CT;
         const int i = i0 + ti, l = l0 + tl;
         if (i >= n || l >= n || i == l || (bi == bl && ti < tl)) continue;
@@ -172,8 +184,24 @@ __global__ void __launch_bounds__(256) cov_syrk_kernel(CovArgs a)
 
 void launch_cov_update(const CovArgs &a, hipStream_t s)
 {
-    const int nt = (a.n + CT - 1) / CT;
-    hipLaunchKernelGGL(cov_syrk_kernel, dim3(nt * (nt + 1) / 2), dim3(256), 0, s, a);
+    const int nt = (a.n + CT - 1) / CT, tiles = nt * (nt + 1) / 2;
+    const bool small = (long)a.K * a.n < (1l << 30);
+    // up to a tile a CU (256), eight waves share it: two a SIMD, half the
+    // samples each (K = 1000, n = 462: 21.9 us against 29.9 with four).  Past
+    // that two tiles share a CU and eight waves only add to the reduction
+    // (K = 256, n = 1400: 30.7 us against 28.3); at 128 samples or fewer four
+    // waves have one step each already (K = 64, n = 280: 14.6 us either way).
+    if (tiles <= 256 && a.K > 16 * CG) {
+        if (small)
+            hipLaunchKernelGGL((cov_syrk_kernel<8, uint32_t>), dim3(tiles), dim3(512), 0, s, a);
+        else
+            hipLaunchKernelGGL((cov_syrk_kernel<8, long>), dim3(tiles), dim3(512), 0, s, a);
+    } else {
+        if (small)
+            hipLaunchKernelGGL((cov_syrk_kernel<4, uint32_t>), dim3(tiles), dim3(256), 0, s, a);
+        else
+            hipLaunchKernelGGL((cov_syrk_kernel<4, long>), dim3(tiles), dim3(256), 0, s, a);
+    }
 }
 
 // ------------------------------------------------------------------ Cholesky
