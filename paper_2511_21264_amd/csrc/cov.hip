@@ -15,7 +15,7 @@
 //                      and A_cb L_bb^-T itself and subtracts their product
 //                      (FP64 MFMA); the tile (r, r) also stores its panel block
 //                      as the factor, and the workgroup of the next diagonal
-//                      tile factors and inverts it in registers once updated
+//                      tile factors and inverts it in one wave's registers
 //   sample_*_kernel    U = clip(nu + Z L^T, +-u_max): both factors as three
 //                      bf16 parts in operand order, bf16 MFMA 16x16x32 over
 //                      32 x 64 tiles, skipping the zero upper triangle of L
@@ -219,139 +219,123 @@ __global__ void __launch_bounds__(256) chol_init_kernel(CholArgs a)
     if (a.reset_flag && blockIdx.x == 0 && threadIdx.x == 0) *a.flag = a.n;
 }
 
-// element i (0..3) of a four-vector without dynamic indexing (sum of
-// selects: no lookup table, no scratch)
-__device__ __forceinline__ double pick4(const double v[4], int i)
+// x of lane N of each row of 16 lanes, on all of them
+template <int N>
+__device__ __forceinline__ double row_bcast(double x)
 {
-    return (i == 0 ? v[0] : 0.0) + (i == 1 ? v[1] : 0.0) + (i == 2 ? v[2] : 0.0) + (i == 3 ? v[3] : 0.0);
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), 0x150 + N, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), 0x150 + N, 0xF, 0xF, true);
+    return __hiloint2double(hi, lo);
 }
 
-// Factor the diagonal block held in s (lower triangle valid for rows and
-// columns < nbk), invert it, and store the factor block of columns c0.. into
-// L and the inverse into Linv.  256 threads: thread t keeps the
-// entries (t / 32 + 8 k, t % 32), k = 0..3, of the block and of its inverse
-// in registers.  Columns go four at a time: their owners publish them (and
-// the four matching rows of the inverse) to LDS, one barrier, then every
-// thread factors the 4 x 4 diagonal block itself, forms its rows of the
-// panel by forward substitution and applies the rank-4 update to its
-// entries; rows of X = L^-1 follow by forward elimination of L X = I.  The
-// published panels alternate between two buffers, so one barrier per four
-// columns suffices.
-__device__ void factor_block(const double (*s)[CB + 1], double (*cbuf)[4][CB], double (*xbuf)[4][CB], int nbk,
-                             int c0b, const CholArgs &a, double *Linv)
+// a[k] -= l bcast(l, lane k), e[k] -= m bcast(l, lane k) for k = K .. 15
+template <int K>
+__device__ __forceinline__ void rank1(double (&a)[16], double (&e)[16], double l, double m)
 {
-    const int t = threadIdx.x, q = t & 31, r0 = t >> 5;
-    const int n = a.n;
-    double sv[4], xv[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int r = r0 + 8 * k;
-        if (r >= nbk || q >= nbk)
-            sv[k] = r == q ? 1.0 : 0.0;  // rows and columns past n: the identity
-        else
-            sv[k] = q <= r ? s[r][q] : 0.0;
-        xv[k] = r == q ? 1.0 : 0.0;
+    if constexpr (K < 16) {
+        const double lk = row_bcast<K>(l);
+        a[K] = fma(-l, lk, a[K]);
+        e[K] = fma(-m, lk, e[K]);
+        rank1<K + 1>(a, e, l, m);
     }
-    int bad = -1;
+}
+
+// Columns J .. 15 of the factorization of a 16 x 16 block: lane r of each row
+// of 16 lanes holds row r of the block (a) and a row e of its own that becomes
+// e L^-T.  A pivot that is not positive and finite makes its column NaN.
+template <int J>
+__device__ __forceinline__ void factor16(double (&a)[16], double (&e)[16])
+{
+    if constexpr (J < 16) {
+        const double id = rsqrt(row_bcast<J>(a[J]));
+        a[J] *= id;
+        e[J] *= id;
+        rank1<J + 1>(a, e, a[J], e[J]);
+        factor16<J + 1>(a, e);
+    }
+}
+
+// Factor the diagonal block held in s (zero above the diagonal, the identity
+// in rows and columns past nbk), invert it, and store the factor block of
+// columns c0b.. into L and the inverse into Linv.  256 threads; x is scratch.
+//
+// A serial chain: pivot, reciprocal root, column, next pivot.  One wave runs
+// it on two halves of 16, in registers, with broadcasts inside rows of 16
+// lanes (no LDS and no barrier between columns), every row of lanes on the
+// same block and each with 16 more rows that take the same column steps: the
+// rows below it (lanes 0-15) and those of X^T = I L^-T (the others, X = L^-1).
+// Between the halves L21 L21^T and X11^T L21^T leave the second one's rows, by
+// FP64 MFMA.  The loop over the halves stays rolled: a launch runs this once,
+// so code is fetched cold, and size is time.  n = 896 (28 blocks): 427 us with
+// four waves on groups of four columns (30 KB of code) -> 326 us (6 KB), with
+// the tile fetched along with its operands; both halves written out, 658 us.
+__device__ void factor_block(double (*s)[CB + 1], double (*x)[CB + 1], int nbk, int c0b, const CholArgs &arg,
+                             double *Linv)
+{
+    const int n = arg.n;
+    for (int i = threadIdx.x; i < CB * CB; i += 256) x[i / CB][i % CB] = i / CB == i % CB ? 1.0 : 0.0;
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        const int lane = threadIdx.x, r = lane & 15, g = lane >> 4;
+        double *er = g == 0 ? s[16 + r] : x[16 * (min(g, 2) - 1) + r];
+#pragma unroll 1
+        for (int h = 0; h < CB; h += 16) {
+            double a[16], e[16];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int c0 = 4 * i, par = i & 1, kb = i >> 1;  // rows c0..c0+3 are k = kb of threads r0 = c0 & 7 ..
-        if (q >= c0 && q < c0 + 4) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) cbuf[par][q - c0][r0 + 8 * k] = sv[k];
-        }
-        {
-            const int rr = r0 + 8 * kb;
-            if (rr >= c0 && rr < c0 + 4) xbuf[par][rr - c0][q] = xv[kb];
-        }
-        __syncthreads();
-        // the 4 x 4 diagonal block, factored (left-looking) by every thread
-        double L4[4][4], id[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            double p = cbuf[par][u][c0 + u];
-#pragma unroll
-            for (int w = 0; w < u; ++w) p -= L4[u][w] * L4[u][w];
-            if (bad < 0 && !(p > 0.0 && p < INFINITY)) bad = c0 + u;
-            id[u] = rsqrt(p);
-            L4[u][u] = p * id[u];
-#pragma unroll
-            for (int v = u + 1; v < 4; ++v) {
-                double x = cbuf[par][u][c0 + v];
-#pragma unroll
-                for (int w = 0; w < u; ++w) x -= L4[v][w] * L4[u][w];
-                L4[v][u] = x * id[u];
+            for (int k = 0; k < 16; ++k) {
+                a[k] = s[h + r][h + k];
+                e[k] = er[h + k];
             }
-        }
-        // panel row r: l[u] = (a_r[u] - sum_{w<u} l[w] L4[u][w]) / L4[u][u]
-        auto panel = [&](int r, double l[4]) {
+            factor16<0>(a, e);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                double x = cbuf[par][u][r];
-#pragma unroll
-                for (int w = 0; w < u; ++w) x -= l[w] * L4[u][w];
-                l[u] = x * id[u];
+            for (int k = 0; k < 16; ++k) {
+                s[h + r][h + k] = a[k];
+                er[h + k] = e[k];
             }
-        };
-        double lq[4], xc[4];
-        panel(q, lq);
-        // rows c0..c0+3 of X at column q
+            wave_lds_sync();
+            if (h == 0) {
+                d4 c, f;  // rows g + 4 v, column r
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            double x = xbuf[par][u][q];
-#pragma unroll
-            for (int w = 0; w < u; ++w) x -= L4[u][w] * xc[w];
-            xc[u] = x * id[u];
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int r = r0 + 8 * k;
-            double lr[4];
-            panel(r, lr);
-            if (r >= c0 + 4) {
-                const double upd = ((sv[k] - lr[0] * lq[0]) - lr[1] * lq[1]) - lr[2] * lq[2] - lr[3] * lq[3];
-                if (q >= c0 + 4 && q <= r)
-                    sv[k] = upd;
-                else if (q >= c0 && q < c0 + 4)
-                    sv[k] = pick4(lr, q - c0);
-                xv[k] = (((xv[k] - lr[0] * xc[0]) - lr[1] * xc[1]) - lr[2] * xc[2]) - lr[3] * xc[3];
-            } else if (r >= c0) {
-                const int u = r - c0;
-                if (q >= c0 && q <= r) {
-                    // L4[u][q - c0]: row u of the lower factor (entries above the diagonal are not read)
-                    const double lu[4] = {u == 0 ? L4[0][0] : (u == 1 ? L4[1][0] : (u == 2 ? L4[2][0] : L4[3][0])),
-                                          u == 1 ? L4[1][1] : (u == 2 ? L4[2][1] : L4[3][1]),
-                                          u == 2 ? L4[2][2] : L4[3][2], L4[3][3]};
-                    sv[k] = pick4(lu, q - c0);
+                for (int v = 0; v < 4; ++v) {
+                    c[v] = s[16 + g + 4 * v][16 + r];
+                    f[v] = 0.0;
                 }
-                xv[k] = pick4(xc, u);
+#pragma unroll
+                for (int k = 0; k < 16; k += 4) {
+                    const double l = s[16 + r][k + g];
+                    c = __builtin_amdgcn_mfma_f64_16x16x4f64(-l, l, c, 0, 0, 0);
+                    f = __builtin_amdgcn_mfma_f64_16x16x4f64(-x[r][k + g], l, f, 0, 0, 0);
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    s[16 + g + 4 * v][16 + r] = c[v];
+                    x[g + 4 * v][16 + r] = f[v];
+                }
+                wave_lds_sync();
             }
         }
+        // the first pivot that was not positive and finite
+        const unsigned long long bad = __ballot(lane < nbk && !(s[lane & (CB - 1)][lane & (CB - 1)] > 0.0));
+        if (lane == 0 && bad != 0 && *arg.flag == n) *arg.flag = c0b + __builtin_ctzll(bad);
     }
-    if (t == 0 && bad >= 0 && bad < nbk && *a.flag == n) *a.flag = c0b + bad;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int r = r0 + 8 * k;
-        Linv[r * CB + q] = xv[k];
-        if (r < nbk && q <= r) {
-            const long e = (long)(c0b + r) * n + c0b + q;
-            a.L[e] = sv[k];
-        }
+    __syncthreads();
+    for (int i = threadIdx.x; i < CB * CB; i += 256) {
+        const int r = i / CB, q = i % CB;
+        Linv[i] = x[q][r];
+        if (r < nbk && q <= r) arg.L[(long)(c0b + r) * n + c0b + q] = s[r][q];
     }
 }
 
 // the first diagonal block (the others are factored by the step before them)
 __global__ void __launch_bounds__(256) chol_diag_kernel(CholArgs a)
 {
-    __shared__ double s[CB][CB + 1];
-    __shared__ double cbuf[2][4][CB], xbuf[2][4][CB];
+    __shared__ double s[CB][CB + 1], x[CB][CB + 1];
     const int n = a.n, nbk = min(CB, n);
     for (int e = threadIdx.x; e < CB * CB; e += 256) {
         const int r = e / CB, q = e % CB;
-        if (r < nbk && q <= r) s[r][q] = a.A[(long)r * n + q];
+        s[r][q] = r < nbk && q <= r ? a.A[(long)r * n + q] : (r == q ? 1.0 : 0.0);
     }
-    __syncthreads();
-    factor_block(s, cbuf, xbuf, nbk, 0, a, a.Linv);
+    factor_block(s, x, nbk, 0, a, a.Linv);
 }
 
 // Step b of the right-looking factorization over the trailing lower tiles
@@ -361,14 +345,13 @@ __global__ void __launch_bounds__(256) chol_diag_kernel(CholArgs a)
 // complete after this update, is factored and inverted right away.  The
 // inverse of block b is read from Linv[b & 1] and that of b + 1 written to
 // the other half, so no workgroup of this launch reads what another writes.
-__global__ void __launch_bounds__(256) chol_step_kernel(CholArgs a, int b)
+__global__ void __launch_bounds__(256, 2) chol_step_kernel(CholArgs a, int b)
 {
     __shared__ double li[CB][CB + 1];
     __shared__ double ar[CB][CB + 1];
     __shared__ double ac[CB][CB + 1];
     __shared__ double pr[CB][CB + 1];
     __shared__ double pc[CB][CB + 1];
-    __shared__ double cbuf[2][4][CB], xbuf[2][4][CB];
     int rr, cc;
     tri_index(blockIdx.x, rr, cc);
     const int rb = b + 1 + rr, cb = b + 1 + cc;
@@ -382,9 +365,15 @@ __global__ void __launch_bounds__(256) chol_step_kernel(CholArgs a, int b)
         ar[x][y] = R0 + x < n ? a.A[(long)(R0 + x) * n + c0 + y] : 0.0;
         if (!diag) ac[x][y] = C0 + x < n ? a.A[(long)(C0 + x) * n + c0 + y] : 0.0;
     }
-    __syncthreads();
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4;
     const int ba = 16 * (wv >> 1), bb = 16 * (wv & 1);
+    double old[4];  // this wave's block of the tile, fetched with the operands
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int x = ba + lq + 4 * v, y = bb + lr;
+        old[v] = R0 + x < n && C0 + y < n ? a.A[(long)(R0 + x) * n + C0 + y] : 0.0;
+    }
+    __syncthreads();
     d4 c1 = {0.0, 0.0, 0.0, 0.0}, c2 = c1;
 #pragma unroll
     for (int kk = 0; kk < CB; kk += 4) {
@@ -409,9 +398,11 @@ __global__ void __launch_bounds__(256) chol_step_kernel(CholArgs a, int b)
         const int x = ba + lq + 4 * v, y = bb + lr;
         if (R0 + x < n && C0 + y < n && (!diag || y <= x)) {
             const long e = (long)(R0 + x) * n + C0 + y;
-            const double nv = a.A[e] - cu[v];
+            const double nv = old[v] - cu[v];
             a.A[e] = nv;
             if (next) ar[x][y] = nv;  // ar is no longer read: the products above are done
+        } else if (next) {
+            ar[x][y] = x == y ? 1.0 : 0.0;
         }
     }
     if (diag) {
@@ -422,10 +413,7 @@ __global__ void __launch_bounds__(256) chol_step_kernel(CholArgs a, int b)
             a.L[eL] = pr[x][y];
         }
     }
-    if (next) {
-        __syncthreads();
-        factor_block(ar, cbuf, xbuf, min(CB, n - R0), R0, a, a.Linv + ((b + 1) & 1) * CB * CB);
-    }
+    if (next) factor_block(ar, li, min(CB, n - R0), R0, a, a.Linv + ((b + 1) & 1) * CB * CB);
 }
 
 void launch_cholesky(const CholArgs &a, hipStream_t s)
