@@ -301,6 +301,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) ro
     for (int i = 0; i < NTERMS; ++i) acc.t[i] = 0.f;
     StepCounters cnt = {0, 0, 0, 0};
     float uprev = 0.f;
+    Sweep sw;
     for (int k = 0; k < a.H; ++k) {
         const DevModel &md = model(a.md);
         float u = 0.f;
@@ -314,7 +315,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) ro
             }
         }
         for (int s = 0; s < nsub; ++s)
-            team_substep<NC, TPW == 1 ? 64 : TEAM, TPW == 1, TASK>(model(a.md), jc, tc, S, u, cnt);
+            team_substep<NC, TPW == 1 ? 64 : TEAM, TPW == 1, TASK>(model(a.md), jc, tc, S, u, cnt, sw);
         team_stage_cost<false, TASK, TPW == 1>(model(a.md), jc, tc, S, u, uprev, k == 0, hist, dist, a.K, acc, cnt);
         uprev = u;
         if (a.xout && a.traj && active && primary) {
@@ -375,21 +376,35 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) ro
     }
 }
 
-// Split mapping: two waves per sample.  Wave 0 (dynamics) owns the state and
-// runs the inertia, factorisation, bias forces and free velocities, then the
-// contact solve, the integration and the kinematics at the new positions;
-// wave 1 (geometry) takes those kinematics and runs, concurrently with wave
-// 0's dynamics, the geom AABBs and the contact sweep, and during wave 0's
-// contact solve the cost of the previous control step.  Two workgroup
-// barriers per substep hand the positions and kinematics to wave 1 (B1) and
-// the contact list to wave 0 (B2); both waves run the same loop nest, so they
-// meet every barrier the same number of times.  Every value equals the
-// wave-per-sample mapping's bit for bit.
-// state handoff: q[14], ball centre[3], contact count, finite flag; the
-// task form also the object's quaternion (SA_QUAT) and qd[14] (SA_QD); the
-// kinematics of the team's 16 lanes, 20 floats each (SA_KIN: a, z, o, o1,
-// and the link frame's x, y)
-constexpr int SA_QUAT = 19, SA_QD = 24, SA_KIN = 40, SPLIT_SA = SA_KIN + 16 * 20;
+// Split mapping: two waves per sample, which share the critical path.  Wave 0
+// (dynamics) owns the arms: inertia, factorisation, bias forces and free
+// velocities, then their integration and the kinematics at the new positions.
+// Wave 1 (geometry) owns the ball: meanwhile it runs the geom AABBs and the
+// contact sweep on the kinematics, the ball's contact and integration, and
+// once per control step the cost of the previous one.  Barriers per substep:
+//   B1  the positions and kinematics are in LDS, for wave 1;
+//   B2  the contact list is in LDS, for wave 0.  Wave 0 meets it within the
+//       dynamics, about where the coarse test ends, or, if that test had found
+//       something near in the substep before (so the sweep ran), after them;
+//   B3  only where an arm is in contact: wave 0 has solved the contacts with
+//       the ball's free velocities and hands back the final ones.
+// Both waves decide on the same values in LDS, so they meet every barrier the
+// same number of times.  Every value equals the wave-per-sample mapping's bit
+// for bit.
+// A substep of a ball on the table takes 6.2 k cycles (dynamics 2.2 k to B2,
+// 1.2 k after, kinematics 1.7 k, handoff 0.6 k; sweep 1.7-2.1 k, ball 2.8 k)
+// where the dynamics wave alone did the ball's step too and the other waited,
+// 8.1 k.  One control step of one sample 42.4 -> 34.0 us; K = 64, H = 20 five
+// iterations 863 -> 722 us; K = 1024, H = 64 ten 15.6 -> 14.3 ms: there a SIMD
+// holds a wave of each kind of two samples and the slowest samples, with arms
+// in contact (12 k cycles), set the end, so both their waves issue ahead.
+// state handoff (SA): q[14], contact count (SA_NC, 0 where the arms are free),
+// finite flag (SA_BAD); for the solve of wave 0 the ball's centre and free
+// velocities (SA_BALL), which it replaces with the final ones, and the
+// object's quaternion; for the task form's cost qd[14]; the kinematics of the
+// team's 16 lanes, 20 floats each (a, z, o, o1, and the link frame's x, y)
+constexpr int SPLIT_LATE = 256;  // flag beside the contact count: the sweep ran, meet B2 late next time
+constexpr int SA_NC = 14, SA_BAD = 15, SA_BALL = 16, SA_QUAT = 28, SA_QD = 32, SA_OUT = 46, SA_KIN = 52, SPLIT_SA = SA_KIN + 16 * 20;
 
 // FRAME: with the link frame's x and y axes
 template <bool FRAME>
@@ -420,6 +435,34 @@ __device__ __forceinline__ void split_get_kin(const float *p, JointKin &k)
         k.y = v3(d.w, e.x, e.y);
     }
 }
+// this wave's part of the state vector: the arms (joint lanes) or the ball
+__device__ __forceinline__ void split_put_state(float *o, const TeamCtx &tc, int d, const TeamState &S, bool ball)
+{
+    if (!ball) {
+        if (tc.joint) {
+            o[XQ + d] = S.q; o[XQD + d] = S.qd; o[XQDES + d] = S.qdes;
+        }
+    } else if (tc.t == 7) {
+        o[XPB] = S.pb.x; o[XPB + 1] = S.pb.y; o[XPB + 2] = S.pb.z;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[XQUAT + i] = S.quat[i];
+        o[XVB] = S.vb.x; o[XVB + 1] = S.vb.y; o[XVB + 2] = S.vb.z;
+        o[XWB] = S.wb.x; o[XWB + 1] = S.wb.y; o[XWB + 2] = S.wb.z;
+    }
+}
+
+// the ball's centre, free velocities and (TASK) orientation, for a solve by
+// the dynamics wave
+template <bool TASK>
+__device__ __forceinline__ void split_put_ball(float *SA, const TeamState &S, V3 vb, V3 wb)
+{
+    float4 *o = reinterpret_cast<float4 *>(SA + SA_BALL);
+    o[0] = make_float4(S.pb.x, S.pb.y, S.pb.z, vb.x);
+    o[1] = make_float4(vb.y, vb.z, wb.x, wb.y);
+    o[2] = make_float4(wb.z, 0.f, 0.f, 0.f);
+    if (TASK) o[3] = make_float4(S.quat[0], S.quat[1], S.quat[2], S.quat[3]);
+}
+
 template <int NC, bool TASK = false>
 __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2, 2))) rollout_split_kernel(RolloutArgs a0, const RolloutArgs *tab, const int *blk,
                                                              int m)
@@ -428,12 +471,8 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2, 2))
     RolloutArgs a;
     int bid;
     block_scene(a0, tab, blk, m, a, bid);
-    const int wave = threadIdx.x >> 6;
-    const bool geo = wave == 1;
-    // the dynamics wave carries each substep's critical path: it issues
-    // ahead of the geometry waves that share its SIMD (priority 2 inside the
-    // general contact solve)
-    if (!geo) __builtin_amdgcn_s_setprio(1);
+    // a scalar, as are the other conditions that barriers stand under
+    const bool geo = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 1;
     const int lane = threadIdx.x & 63;
     const int row = lane >> 4;
     float *blockD = lds + HD_FIELDS, *blockG = blockD + team_lds_floats(NC);
@@ -484,7 +523,7 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2, 2))
     S.wb = v3(x0[XWB], x0[XWB + 1], x0[XWB + 2]);
 #pragma unroll
     for (int i = 0; i < 4; ++i) S.quat[i] = x0[XQUAT + i];
-    const int nsub = a.n_sub > 0 ? a.n_sub : md0.n_sub;
+    const int nsub = __builtin_amdgcn_readfirstlane(a.n_sub > 0 ? a.n_sub : md0.n_sub);
     uint32_t hist = 0u;
     float *dist = a.dist + j;
     CostAcc acc;
@@ -492,6 +531,8 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2, 2))
     for (int i = 0; i < NTERMS; ++i) acc.t[i] = 0.f;
     StepCounters cnt = {0, 0, 0, 0};
     float u1 = 0.f, u2 = 0.f;  // controls of the previous two steps (geometry wave's cost)
+    Sweep sw;
+    bool held = false, late = false;  // an arm was in contact, the pair sweep ran, in the substep before
     // the kinematics at the current positions: formed by the dynamics wave
     // (at x0 here, then after each integration), published for the geometry wave
     JointKin kd;
@@ -499,6 +540,9 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2, 2))
         team_fk<TASK>(jc, S.q, tc.jt, kd);
         if (row == 0) split_put_kin<TASK>(SA + SA_KIN + 20 * tc.t, kd);
     }
+    V3 fvb, fwb;  // the ball's free velocities
+    ball_free<TASK>(md0, S, fvb, fwb);
+    bool put = false;  // the ball is in LDS for this substep: likely to be needed where a sweep ran in the one before
     for (int k = 0; k < a.H; ++k) {
         const DevModel &md = model(a.md);
         float u = 0.f;
@@ -512,104 +556,112 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2, 2))
             }
         }
         for (int s = 0; s < nsub; ++s) {
-            JointKin kk;
-            float v = 0.f;
-            V3 vb, wb;
-            __syncthreads();  // B1: positions of this substep are in SA
+            __syncthreads();  // B1
             if (geo) {
-                if (k > 0 || s > 0) {
-                    if (tc.joint) S.q = SA[d];
-                    S.pb = v3(SA[14], SA[15], SA[16]);
-                    if (TASK) {
-                        if (tc.joint) S.qd = SA[SA_QD + d];
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) S.quat[i] = SA[SA_QUAT + i];
-                    }
+                if (tc.joint && (k > 0 || s > 0)) {
+                    S.q = SA[d];
+                    if (TASK) S.qd = SA[SA_QD + d];
                 }
+                JointKin kk;
                 split_get_kin<TASK>(SA + SA_KIN + 20 * tc.t, kk);
-                const int nc = team_contacts<64, TASK>(model(a.md), tc, kk, S.pb, cnt, S.quat);
-                if (lane == 0) SA[17] = __int_as_float(nc);
+                const DevModel &mg = model(a.md);
+                const int nc = team_contacts<64, TASK>(mg, tc, kk, S.pb, cnt, sw, S.quat);
+                const bool alone = __builtin_amdgcn_readfirstlane(sw.alone) != 0;
+                if (lane == 0) {
+                    SA[SA_NC] = __int_as_float((alone ? 0 : nc) | (sw.published ? SPLIT_LATE : 0));
+                    if (!alone && !put) split_put_ball<TASK>(SA, S, fvb, fwb);
+                }
+                put = sw.published;
+                __syncthreads();  // B2
+                V3 vb = fvb, wb = fwb;
+                // cost of step k - 1 at its post-step state: this substep's positions,
+                // whose geometry and AABBs the contact sweep may just have published
+                if (s == 0 && k > 0)
+                    team_stage_cost<true, TASK>(model(a.md), jc, tc, S, u1, u2, k - 1 == 0, hist, dist, a.K, acc, cnt,
+                                                &kk, sw.published);
+                if (alone) {
+                    ball_alone(model(a.md), tc.LL, S.pb, nc, vb, wb);
+                } else {
+                    __builtin_amdgcn_s_setprio(1);
+                    __syncthreads();  // B3
+                    const float *o = SA + SA_OUT;
+                    vb = v3(o[0], o[1], o[2]);
+                    wb = v3(o[3], o[4], o[5]);
+                }
+                if (alone) __builtin_amdgcn_s_setprio(0);
+                integrate_ball(model(a.md), S, vb, wb);
+                ball_free<TASK>(model(a.md), S, fvb, fwb);
+                if (put && lane == 0) split_put_ball<TASK>(SA, S, fvb, fwb);
             } else {
-                kk = kd;
-                team_dynamics<NC, true, TASK, true>(model(a.md), jc, tc, S, u, kk, v, vb, wb);
-            }
-            __syncthreads();  // B2: the contact list and its count are in LDS
-            if (!geo) {
-                const int nc = __float_as_int(SA[17]);
-                team_finish<NC, true, true, TASK>(model(a.md), tc, S, kk, nc, v, vb, wb);
+                float v = 0.f, Mrow[NJ] = {};
+                const bool row_ready = held;  // the substep before had an arm in contact, and this one likely
+                team_dynamics<NC, true, TASK, true>(model(a.md), jc, tc, S, u, kd, v, [&] {
+                    if (!late) __syncthreads();  // B2
+                }, [&](const float(&Lf)[28]) {
+                    if (held) team_minv_row(tc, Lf, Mrow);
+                });
+                if (late) __syncthreads();  // B2
+                const int word = __builtin_amdgcn_readfirstlane(__float_as_int(SA[SA_NC]));
+                const int nc = word & (SPLIT_LATE - 1);
+                late = (word & SPLIT_LATE) != 0;
+                held = nc > 0;
+                if (held) {
+                    __builtin_amdgcn_s_setprio(2);
+                    const float4 *o = reinterpret_cast<const float4 *>(SA + SA_BALL);
+                    const float4 b0 = o[0], b1 = o[1], b2 = o[2];
+                    S.pb = v3(b0.x, b0.y, b0.z);
+                    V3 vb = v3(b0.w, b1.x, b1.y), wb = v3(b1.z, b1.w, b2.x);
+                    if (TASK) {
+                        const float4 q4 = o[3];
+                        S.quat[0] = q4.x; S.quat[1] = q4.y; S.quat[2] = q4.z; S.quat[3] = q4.w;
+                    }
+                    team_solve<NC, true, TASK>(model(a.md), tc, S, kd, nc, v, vb, wb, Mrow, row_ready);
+                    if (lane == 0) {
+                        float *r = SA + SA_OUT;
+                        r[0] = vb.x; r[1] = vb.y; r[2] = vb.z;
+                        r[3] = wb.x; r[4] = wb.y; r[5] = wb.z;
+                    }
+                    __syncthreads();  // B3
+                } else {
+                    __builtin_amdgcn_s_setprio(0);
+                }
+                S.q = fmaf(model(a.md).h, v, S.q);
+                S.qd = v;
                 team_fk<TASK>(jc, S.q, tc.jt, kd);
                 if (row == 0) split_put_kin<TASK>(SA + SA_KIN + 20 * tc.t, kd);
-                if (tc.joint) SA[d] = S.q;
-                if (lane == 0) { SA[14] = S.pb.x; SA[15] = S.pb.y; SA[16] = S.pb.z; }
-                if (TASK) {
-                    if (tc.joint) SA[SA_QD + d] = S.qd;
-                    if (lane == 0) {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) SA[SA_QUAT + i] = S.quat[i];
-                    }
+                if (tc.joint) {
+                    SA[d] = S.q;
+                    if (TASK) SA[SA_QD + d] = S.qd;
                 }
-                if (s == nsub - 1 && a.xout && a.traj && row == 0) {
-                    float *o = a.xout + ((long)j * a.H + k) * NX;
-                    if (tc.joint) {
-                        o[XQ + d] = S.q; o[XQD + d] = S.qd; o[XQDES + d] = S.qdes;
-                    } else if (tc.arm == 0) {
-                        o[XPB] = S.pb.x; o[XPB + 1] = S.pb.y; o[XPB + 2] = S.pb.z;
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) o[XQUAT + i] = S.quat[i];
-                        o[XVB] = S.vb.x; o[XVB + 1] = S.vb.y; o[XVB + 2] = S.vb.z;
-                        o[XWB] = S.wb.x; o[XWB + 1] = S.wb.y; o[XWB + 2] = S.wb.z;
-                    }
-                }
-            } else if (s == 0 && k > 0) {
-                // cost of step k - 1 at its post-step state: this substep's positions,
-                // whose geometry and AABBs the contact sweep has just published
-                team_stage_cost<true, TASK>(model(a.md), jc, tc, S, u1, u2, k - 1 == 0, hist, dist, a.K, acc, cnt,
-                                            &kk);
             }
+            if (s == nsub - 1 && a.xout && a.traj && row == 0)
+                split_put_state(a.xout + ((long)j * a.H + k) * NX, tc, d, S, geo);
         }
         u2 = u1;
         u1 = u;
     }
     // the final state: dynamics wave publishes it with its finiteness
     const DevModel &md = model(a.md);
+    if (a.xout && !a.traj && row == 0) split_put_state(a.xout + (long)j * NX, tc, d, S, geo);
     if (!geo) {
-        float bad = (isfinite(S.q) && isfinite(S.qd) && isfinite(S.qdes)) ? 0.f : 1.f;
-        bad += (isfinite(S.pb.x) && isfinite(S.pb.y) && isfinite(S.pb.z) && isfinite(S.vb.x) && isfinite(S.vb.y) &&
-                isfinite(S.vb.z) && isfinite(S.wb.x) && isfinite(S.wb.y) && isfinite(S.wb.z) &&
-                isfinite(S.quat[0]) && isfinite(S.quat[1]) && isfinite(S.quat[2]) && isfinite(S.quat[3]))
-                   ? 0.f
-                   : 1.f;
-        bad = team_sum(bad);
-        if (lane == 0) SA[18] = bad;
-        if (a.xout && !a.traj && row == 0) {
-            float *o = a.xout + (long)j * NX;
-            if (tc.joint) {
-                o[XQ + d] = S.q; o[XQD + d] = S.qd; o[XQDES + d] = S.qdes;
-            } else if (tc.arm == 0) {
-                o[XPB] = S.pb.x; o[XPB + 1] = S.pb.y; o[XPB + 2] = S.pb.z;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) o[XQUAT + i] = S.quat[i];
-                o[XVB] = S.vb.x; o[XVB + 1] = S.vb.y; o[XVB + 2] = S.vb.z;
-                o[XWB] = S.wb.x; o[XWB + 1] = S.wb.y; o[XWB + 2] = S.wb.z;
-            }
-        }
+        const float bad = team_sum((isfinite(S.q) && isfinite(S.qd) && isfinite(S.qdes)) ? 0.f : 1.f);
+        if (lane == 0) SA[SA_BAD] = bad;
     }
     __syncthreads();  // final positions and the finiteness flag are in SA
     if (!geo) return;
-    if (tc.joint) S.q = SA[d];
-    S.pb = v3(SA[14], SA[15], SA[16]);
-    if (TASK) {
-        if (tc.joint) S.qd = SA[SA_QD + d];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) S.quat[i] = SA[SA_QUAT + i];
+    if (tc.joint) {
+        S.q = SA[d];
+        if (TASK) S.qd = SA[SA_QD + d];
     }
     team_stage_cost<false, TASK>(md, jc, tc, S, u1, u2, a.H - 1 == 0, hist, dist, a.K, acc, cnt);
     CostAcc tot;
 #pragma unroll
     for (int i = 0; i < NTERMS; ++i) tot.t[i] = (TASK || i < 7) ? team_sum(acc.t[i]) : 0.f;
     const float c = total_cost<TASK>(md, tot);
-    const float bad = SA[18];
-    const bool finite = isfinite(c) && !(bad > 0.f) && bad == bad;
+    const bool finite = isfinite(c) && SA[SA_BAD] == 0.f && isfinite(S.pb.x) && isfinite(S.pb.y) && isfinite(S.pb.z) &&
+                        isfinite(S.vb.x) && isfinite(S.vb.y) && isfinite(S.vb.z) && isfinite(S.wb.x) &&
+                        isfinite(S.wb.y) && isfinite(S.wb.z) && isfinite(S.quat[0]) && isfinite(S.quat[1]) &&
+                        isfinite(S.quat[2]) && isfinite(S.quat[3]);
     const float np = wave_sum((float)cnt.np_tests), nbx = wave_sum((float)cnt.box_tests);
     if (lane == 0) {
         a.costs[j] = finite ? c : INFINITY;

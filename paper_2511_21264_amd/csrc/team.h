@@ -758,7 +758,8 @@ __device__ inline int team_collect(const DevModel &md, float *tl, const float *h
             }
             n = min((int)__popcll(gm), cap);
         }
-        auto narrow_block = [&](bool ov, int gab, bool first) {
+        // later: the lanes whose pairs come after those of all others
+        auto narrow_block = [&](bool ov, int gab, bool first, uint64_t later) {
             const uint64_t om = __ballot(ov);
             if (om == 0ull) return;
             // the ball on the table and nothing else near: pair 0 of the list,
@@ -794,7 +795,8 @@ __device__ inline int team_collect(const DevModel &md, float *tl, const float *h
             }
             const uint64_t gm = __ballot(hit);
             if (hit) {
-                const int slot = n + __popcll(gm & below);
+                const bool lt = (later >> li) & 1ull;
+                const int slot = n + __popcll(gm & ~later & (lt ? ~0ull : below)) + (lt ? __popcll(gm & later & below) : 0);
                 if (slot < md.n_cmax) {
                     LL.at(slot, 0) = __int_as_float(ga);
                     LL.at(slot, 1) = __int_as_float(gb);
@@ -811,8 +813,19 @@ __device__ inline int team_collect(const DevModel &md, float *tl, const float *h
             const int g1 = __float_as_int(hd[HD_PAIR + min(p1, np - 1)]);
             const bool ov0 = (p0 < np) & !(box & (g0 == OBJ_TABLE)) & pair_overlap(tl, hd, g0, 0.f);
             const bool ov1 = (p1 < np) & !(box & (g1 == OBJ_TABLE)) & pair_overlap(tl, hd, g1, 0.f);
-            narrow_block(ov0, g0, base == 0);
-            narrow_block(ov1, g1, false);
+            // in contact both blocks mostly have something near: one pass over
+            // the narrowphase's branches where no lane has a pair in each
+            const uint64_t m0 = __ballot(ov0), m1 = __ballot(ov1);
+            const bool both = m0 != 0ull && m1 != 0ull && (m0 & m1) == 0ull;
+            bool ov = both ? ov0 | ov1 : ov0;
+            int gab = both && !ov0 ? g1 : g0;
+#pragma unroll 1
+            for (int pass = 0;; ++pass) {
+                narrow_block(ov, gab, base == 0 && pass == 0 && !both, both ? m1 : 0ull);
+                if (both || m1 == 0ull || pass == 1) break;
+                ov = ov1;
+                gab = g1;
+            }
         }
         return n;
     }
@@ -1260,10 +1273,6 @@ __device__ __forceinline__ float normal_joint(uint32_t key0, uint32_t key1, uint
 }
 
 
-// Dynamics half of a substep (before contacts): PD target, kinematics,
-// joint-space inertia and its factor (parked for the contact path), bias
-// forces and the free velocities (v of this lane's joint; ball vb with
-// gravity; wb).  k receives this lane's kinematics at the current positions.
 // the team's contact-solve area: per-contact frames E, then Delassus blocks,
 // then the row matrix A (its first 248 floats double as the mass-matrix
 // exchange of team_mass_rows, which runs before any solve of the substep)
@@ -1272,10 +1281,23 @@ __device__ __forceinline__ float *team_solve_area(float *tl) { return tl + TG_FI
 template <int NC>
 __device__ __forceinline__ float *team_row_area(float *tl) { return team_solve_area<NC>(tl) + 20 * NC + 9 * NC * NC; }
 
-// HAVE_K: k already holds the kinematics at S.q
-template <int NC, bool ROWS = false, bool TASK = false, bool HAVE_K = false>
-__device__ inline void team_dynamics(const DevModel &md, const JointConst &jc, const TeamCtx &tc, TeamState &S,
-                                     float u, JointKin &k, float &v, V3 &vb, V3 &wb)
+// the ball's free velocities: vb with gravity; wb (a box object: with its
+// gyroscopic step)
+template <bool TASK = false>
+__device__ __forceinline__ void ball_free(const DevModel &md, const TeamState &S, V3 &vb, V3 &wb)
+{
+    vb = v3(S.vb.x, S.vb.y, S.vb.z - md.h * md.g);
+    wb = (TASK && md.obj_box) ? obj_free_w(md, S.quat, S.wb) : S.wb;
+}
+
+// Dynamics of the arms before contacts: PD target, kinematics, joint-space
+// inertia and its factor (parked for the contact path), bias forces and the
+// free velocity v of this lane's joint.  k receives this lane's kinematics at
+// the current positions.  HAVE_K: k already holds them.  mid() runs about three
+// quarters of the way through, late(factor) at the end.
+template <int NC, bool ROWS = false, bool TASK = false, bool HAVE_K = false, typename Mid, typename Late>
+__device__ __forceinline__ void team_dynamics(const DevModel &md, const JointConst &jc, const TeamCtx &tc,
+                                              TeamState &S, float u, JointKin &k, float &v, Mid mid, Late late)
 {
     static_assert(16 * NC * NC >= 248, "the row area holds the mass-matrix exchange");
     const float h = md.h;
@@ -1294,6 +1316,7 @@ __device__ inline void team_dynamics(const DevModel &md, const JointConst &jc, c
     const float c = team_rnea(md, jc, k, S.qd, jt, md.gravcomp == 0);
     const float tau = clampf(md.kp * (S.qdes - S.q) + md.kd * (u - S.qd), -md.tau_max, md.tau_max);
     const float rhs = h * (tau - md.damp * S.qd - c);
+    mid();
     float xs[NJ];
     static_for<NJ>([&](auto ic) {
         constexpr int i = decltype(ic)::value;
@@ -1301,8 +1324,6 @@ __device__ inline void team_dynamics(const DevModel &md, const JointConst &jc, c
     });
     chol7_solve(Lp, xs);
     v = S.qd + pick7(xs, jt);
-    vb = v3(S.vb.x, S.vb.y, S.vb.z - h * md.g);
-    wb = (TASK && md.obj_box) ? obj_free_w(md, S.quat, S.wb) : S.wb;
     // park the factor for the contact solve (the team keeps the joint axes in
     // registers); it is replicated on the segment: its first lane parks it
     if (jt == 0) {
@@ -1310,23 +1331,47 @@ __device__ inline void team_dynamics(const DevModel &md, const JointConst &jc, c
 #pragma unroll
         for (int e = 0; e < 7; ++e) o[e] = make_float4(Lp[4 * e], Lp[4 * e + 1], Lp[4 * e + 2], Lp[4 * e + 3]);
     }
+    late(Lp);
 }
 
+// true when the substep's only contact is the ball against the table or a
+// box: the arms are untouched and the ball's solve needs no arm data
+__device__ __forceinline__ bool ball_only_contact(const LaneList &LL, int nc)
+{
+    return nc == 1 && __float_as_int(LL.at(0, 0)) == G_BALL &&
+           (__float_as_int(LL.at(0, 1)) == G_TABLE || __float_as_int(LL.at(0, 1)) >= G_BOX);
+}
+
+// true when the substep's contacts leave the arms alone (none, or the ball's
+// only one): the ball's step then needs nothing of theirs
+template <bool TASK = false>
+__device__ __forceinline__ bool arms_free(const DevModel &md, const LaneList &LL, int nc)
+{
+    return nc == 0 || (!(TASK && md.obj_box) && ball_only_contact(LL, nc));
+}
 
 // Geometry half: publish the kinematics and ball centre, the geom AABBs, and
 // sweep the candidate pairs into the contact list (tc.LL); returns the count.
+// Where the coarse test finds nothing near anything but the ball and the
+// table (in any team of the wave), there is no geometry to publish and no
+// sweep.  A team a wave tries it again only after three more substeps without
+// an arm in contact where it fails (where it fails, it mostly fails on).
+struct Sweep {
+    int skip = 0;          // substeps to go without the coarse test
+    bool published = true; // the geometry of this substep is in LDS
+    bool alone = false;    // its contacts leave the arms alone
+};
 template <int G, bool TASK = false>
 __device__ inline int team_contacts(const DevModel &md, const TeamCtx &tc, const JointKin &k, V3 pb,
-                                    StepCounters &cnt, const float *q = nullptr)
+                                    StepCounters &cnt, Sweep &sw, const float *q = nullptr)
 {
-    if (G == TEAM) {
-        // nothing near anything but the ball and the table, in any team of
-        // the wave: no geometry to publish, no sweep; the ball's contact as
-        // sphere_plane forms it
+    sw.published = true;
+    if (!TASK && sw.skip == 0) {  // (a box object is no sphere)
         if (__ballot(team_coarse<false>(md, tc.hd, k, pb, tc.jt, tc.t, 0.f)) == 0ull) {
+            // the ball's contact as sphere_plane forms it
             const float phi = pb.z - tc.hd[HD_RAD + 8];
             const int nc = min(phi < 0.f ? 1 : 0, md.n_cmax);
-            if (tc.t == 0) {
+            if (tc.li == 0) {
                 if (phi <= 0.f && md.n_cmax > 0) {
                     ++cnt.np_tests;
                     tc.LL.at(0, 0) = __int_as_float(G_BALL);
@@ -1339,9 +1384,13 @@ __device__ inline int team_contacts(const DevModel &md, const TeamCtx &tc, const
                 if (nc >= md.n_cmax) ++cnt.overflow;
             }
             wave_lds_sync();
+            sw.published = false;
+            sw.alone = true;
             return nc;
         }
+        if (G != TEAM) sw.skip = 4;
     }
+    if (!TASK && G != TEAM) --sw.skip;
     team_publish_geom_aabb<TASK>(tc.tl, tc.hd, k, pb, tc.arm, tc.jt, &md, q);
     const int nc = team_collect<G, TASK>(md, tc.tl, tc.hd, tc.LL, tc.li, tc.gshift, cnt);
     if (tc.t == 0) {
@@ -1349,6 +1398,8 @@ __device__ inline int team_contacts(const DevModel &md, const TeamCtx &tc, const
         if (nc >= md.n_cmax) ++cnt.overflow;
     }
     wave_lds_sync();
+    sw.alone = arms_free<TASK>(md, tc.LL, nc);
+    if (!TASK && G != TEAM && !sw.alone) sw.skip = 3;
     return nc;
 }
 
@@ -1382,14 +1433,6 @@ __device__ __forceinline__ void integrate_ball(const DevModel &md, TeamState &S,
     S.quat[3] = nv.z * inv;
 }
 
-// true when the substep's only contact is the ball against the table or a
-// box: the arms are untouched and the ball's solve needs no arm data
-__device__ __forceinline__ bool ball_only_contact(const LaneList &LL, int nc)
-{
-    return nc == 1 && __float_as_int(LL.at(0, 0)) == G_BALL &&
-           (__float_as_int(LL.at(0, 1)) == G_TABLE || __float_as_int(LL.at(0, 1)) >= G_BOX);
-}
-
 // element i of a register array (i uniform over a 16-lane row)
 template <int N>
 __device__ __forceinline__ V3 pick_v3(const V3 (&a)[N], int i)
@@ -1406,6 +1449,19 @@ __device__ __forceinline__ int row_bits(uint64_t b)
     return (int)((b & 1ull) | ((b >> 15) & 2ull) | ((b >> 30) & 4ull) | ((b >> 45) & 8ull));
 }
 
+// this lane's row of Mt^-1 of its arm from the factor (zero on lanes without
+// a joint)
+__device__ __forceinline__ void team_minv_row(const TeamCtx &tc, const float Lf[28], float Minv[NJ])
+{
+#pragma unroll
+    for (int e = 0; e < NJ; ++e) Minv[e] = (tc.joint && e == tc.jt) ? 1.f : 0.f;
+    chol7_solve(Lf, Minv);
+    if (!tc.joint) {
+#pragma unroll
+        for (int e = 0; e < NJ; ++e) Minv[e] = 0.f;
+    }
+}
+
 // The same solve for a wave whose four 16-lane rows all carry one team (one
 // sample a wave), nc <= 4: the per-contact and per-pair work is spread over
 // the rows instead of repeated on each.  Row s builds contact s's frame and
@@ -1416,7 +1472,8 @@ __device__ __forceinline__ int row_bits(uint64_t b)
 // bit for bit.
 template <int NC, bool TASK = false>
 __device__ inline void team_contact_solve_rows(const DevModel &md, const TeamCtx &tc, const JointKin &k, V3 pb, int nc,
-                                               float &v, V3 &vb, V3 &wb, const float *Wo = nullptr)
+                                               float &v, V3 &vb, V3 &wb, const float *Wo = nullptr,
+                                               const float *Mrow = nullptr, bool have_row = false)
 {
     const bool box = TASK && md.obj_box;  // Wo: the box object's world inverse inertia
     constexpr int MR = 4 * NC;
@@ -1488,14 +1545,13 @@ __device__ inline void team_contact_solve_rows(const DevModel &md, const TeamCtx
 #pragma unroll
     for (int e = 0; e < NJ; ++e) Minv[e] = 0.f;
     if (any_arm) {
-        float Lf[28];
-        team_parked_factor(tc.pk, tc.arm, Lf);
+        if (have_row) {
 #pragma unroll
-        for (int e = 0; e < NJ; ++e) Minv[e] = (tc.joint && e == tc.jt) ? 1.f : 0.f;
-        chol7_solve(Lf, Minv);
-        if (!tc.joint) {
-#pragma unroll
-            for (int e = 0; e < NJ; ++e) Minv[e] = 0.f;
+            for (int e = 0; e < NJ; ++e) Minv[e] = Mrow[e];
+        } else {
+            float Lf[28];
+            team_parked_factor(tc.pk, tc.arm, Lf);
+            team_minv_row(tc, Lf, Minv);
         }
     }
     // row t: row d of Mt^-1 J_t^T, parked by contact and lane
@@ -1618,79 +1674,84 @@ __device__ inline void team_contact_solve_rows(const DevModel &md, const TeamCtx
     }
 }
 
-// Contact solve and semi-implicit Euler: the end of a substep.  ROWS: the
-// wave's four 16-lane rows carry one team, so a solve of up to four contacts
-// spreads its per-contact work over them.  PRIO: the caller runs at wave
-// priority 1 and the general solve at 2 (issue priority only; the results
-// do not change): a launch lasts as long as its slowest samples, which are
-// the ones that spend many substeps in this solve.
-template <int NC, bool ROWS = false, bool PRIO = false, bool TASK = false>
-__device__ inline void team_finish(const DevModel &md, const TeamCtx &tc, TeamState &S, const JointKin &k, int nc,
-                                   float v, V3 vb, V3 wb)
+// the ball's post-contact velocities where arms_free
+__device__ __forceinline__ void ball_alone(const DevModel &md, const LaneList &LL, V3 pb, int nc, V3 &vb, V3 &wb)
 {
-    const float h = md.h;
-    const bool box = TASK && md.obj_box;
+    if (nc == 0) return;
+    if (__float_as_int(LL.at(0, 1)) == G_TABLE)
+        table_contact_solve(md, LL.at(0, 2), LL.at(0, 8) - pb.z, vb, wb);
+    else
+        ball_contact_solve(md, LL, pb, vb, wb);
+}
+
+// The contact solve in general.  ROWS: the wave's four 16-lane rows carry one
+// team, so a solve of up to four contacts spreads its per-contact work over
+// them.  Mrow, have_row: the lane's row of Mt^-1, where formed before.
+template <int NC, bool ROWS = false, bool TASK = false>
+__device__ __forceinline__ void team_solve(const DevModel &md, const TeamCtx &tc, const TeamState &S,
+                                           const JointKin &k, int nc, float &v, V3 &vb, V3 &wb,
+                                           const float *Mrow = nullptr, bool have_row = false)
+{
     float W[9];
-    if (box) obj_world_inv_inertia(md, S.quat, W);
-    if (!box && ball_only_contact(tc.LL, nc)) {
-        if (__float_as_int(tc.LL.at(0, 1)) == G_TABLE)
-            table_contact_solve(md, tc.LL.at(0, 2), tc.LL.at(0, 8) - S.pb.z, vb, wb);
-        else
-            ball_contact_solve(md, tc.LL, S.pb, vb, wb);
-    } else if (ROWS && nc > 0 && nc <= 4) {
-        if (PRIO) __builtin_amdgcn_s_setprio(2);
-        team_contact_solve_rows<NC, TASK>(md, tc, k, S.pb, nc, v, vb, wb, W);
-        if (PRIO) __builtin_amdgcn_s_setprio(1);
-    } else if (nc > 0)
+    if (TASK && md.obj_box) obj_world_inv_inertia(md, S.quat, W);
+    if (ROWS && nc <= 4) {
+        team_contact_solve_rows<NC, TASK>(md, tc, k, S.pb, nc, v, vb, wb, W, Mrow, have_row);
+    } else {
         team_contact_solve<NC, TASK>(md, tc, k, S.pb, nc, v, vb, wb, W);
-    S.q = fmaf(h, v, S.q);
-    S.qd = v;
-    integrate_ball(md, S, vb, wb);
+    }
 }
 
 // One physics substep of a team: dynamics, contacts, solve, integration.
 template <int NC, int G, bool ROWS = false, bool TASK = false>
 __device__ inline void team_substep(const DevModel &md, const JointConst &jc, const TeamCtx &tc, TeamState &S,
-                                    float u, StepCounters &cnt)
+                                    float u, StepCounters &cnt, Sweep &sw)
 {
     JointKin k;
     float v;
     V3 vb, wb;
-    team_dynamics<NC, ROWS, TASK>(md, jc, tc, S, u, k, v, vb, wb);
-    const int nc = team_contacts<G, TASK>(md, tc, k, S.pb, cnt, S.quat);
-    team_finish<NC, ROWS, false, TASK>(md, tc, S, k, nc, v, vb, wb);
+    team_dynamics<NC, ROWS, TASK>(md, jc, tc, S, u, k, v, [] {}, [](const float(&)[28]) {});
+    ball_free<TASK>(md, S, vb, wb);
+    const int nc = team_contacts<G, TASK>(md, tc, k, S.pb, cnt, sw, S.quat);
+    if (sw.alone)
+        ball_alone(md, tc.LL, S.pb, nc, vb, wb);
+    else
+        team_solve<NC, ROWS, TASK>(md, tc, S, k, nc, v, vb, wb);
+    // semi-implicit Euler
+    S.q = fmaf(md.h, v, S.q);
+    S.qd = v;
+    integrate_ball(md, S, vb, wb);
 }
 
 // per-control-step cost at the post-step state; lane 0 accumulates the stage
 // terms, joint lanes the smoothness, every lane its share of the cost pairs.
-// PUBLISHED: the team's geometry and AABBs in LDS already belong to this
-// state (a contact sweep at the same positions wrote them).
-// TASK: the further terms too (kin: this state's joint kinematics when
-// PUBLISHED; a box object's AABB is published with the geometry).
+// AFTER: a contact sweep at the same positions has run: kin holds this state's
+// joint kinematics, and where published its geometry and AABBs are in LDS.
+// TASK: the further terms too (a box object's AABB is published with the
+// geometry).
 // WIDE: one team a wave.  No cost pair within the margin, the common case,
-// is found out first (WIDE: a pair a lane over the whole wave; else the coarse
-// test), and the walk over the pairs, six blocks with 3 boxes, skipped.
-template <bool PUBLISHED = false, bool TASK = false, bool WIDE = true>
+// is found out first (by the coarse test, before anything is published, and
+// WIDE by a pair a lane over the whole wave), and the walk over the pairs, six
+// blocks with 3 boxes, skipped.
+template <bool AFTER = false, bool TASK = false, bool WIDE = true>
 __device__ inline void team_stage_cost(const DevModel &md, const JointConst &jc, const TeamCtx &tc,
                                        const TeamState &S, float u, float uprev, bool first, uint32_t &hist,
                                        float *dist, long stride, CostAcc &acc, StepCounters &cnt,
-                                       const JointKin *kin = nullptr)
+                                       const JointKin *kin = nullptr, bool published = false)
 {
     JointKin k;
     bool near = true;
     V3 p1, p2;  // the pads
     const float *tl = tc.tl;
-    if (!PUBLISHED) {
+    if (AFTER)
+        k = *kin;
+    else
         team_fk<TASK>(jc, S.q, tc.jt, k);
-        if (!WIDE) near = __ballot(team_coarse<true>(md, tc.hd, k, S.pb, tc.jt, tc.t, md.m_c)) != 0ull;
+    if (!(AFTER && published)) {
+        if (!TASK) near = __ballot(team_coarse<true>(md, tc.hd, k, S.pb, tc.jt, tc.t, md.m_c)) != 0ull;
         if (near) team_publish_geom_aabb<TASK>(tc.tl, tc.hd, k, S.pb, tc.arm, tc.jt, &md, S.quat);
-        p1 = v3(row_bcast<6>(k.o1.x), row_bcast<6>(k.o1.y), row_bcast<6>(k.o1.z));
-        p2 = v3(row_bcast<14>(k.o1.x), row_bcast<14>(k.o1.y), row_bcast<14>(k.o1.z));
-    } else {
-        if (TASK) k = *kin;
-        p1 = v3(tl[TG_PTS + 21], tl[TG_PTS + 22], tl[TG_PTS + 23]);
-        p2 = v3(tl[TG_PTS + 45], tl[TG_PTS + 46], tl[TG_PTS + 47]);
     }
+    p1 = v3(row_bcast<6>(k.o1.x), row_bcast<6>(k.o1.y), row_bcast<6>(k.o1.z));
+    p2 = v3(row_bcast<14>(k.o1.x), row_bcast<14>(k.o1.y), row_bcast<14>(k.o1.z));
     if (TASK && md.ext) {
         // joint deviation (a team sum), pad velocities v_a = sum_j qd_j a_j x
         // (p_a - o_j) as segment contributions summed with arm 2's negated,
@@ -1740,7 +1801,7 @@ __device__ inline void team_stage_cost(const DevModel &md, const JointConst &jc,
         acc.t[4] = fmaf(du, du, acc.t[4]);
     }
     const int nd = md.n_cost, first_pair = md.n_pairs - md.n_cost;
-    if (WIDE) {
+    if (WIDE && near) {
         bool ov = false;
         for (int i = tc.lane; i < nd; i += 64)
             ov |= pair_overlap(tl, tc.hd, __float_as_int(tc.hd[HD_PAIR + first_pair + i]), md.m_c);
