@@ -684,11 +684,14 @@ int pick_mapping(int K, int requested)
         requested == MAP_TASK || requested == MAP_TASK_WAVE || requested == MAP_TASK_SPLIT)
         return requested;
     // the chip holds 1024 SIMDs: up to 2 waves per SIMD two waves per sample
-    // give the shortest steps (at K = 1024, H = 64: 1.90 against 2.21 ms a
-    // wave per sample), up to ~2 samples per SIMD one wave per sample (at
-    // 2048: 2.77 against 4.14 ms); below 64 k samples a 16-lane team per
-    // sample (one lane per sample fills too few waves: at 32 k it is 1.5 x
-    // slower); from 64 k on one lane per sample has the highest throughput
+    // give the shortest steps (two iterations at K = 1024, H = 64: 2.33 against
+    // 2.90 ms a wave per sample, 6.04 against 6.73 with arms in contact), up to
+    // ~2 samples per SIMD one wave per sample (at 1100: 3.56 against 3.53 and
+    // 8.27 against 9.47, at 2048 3.61 against 4.63 and 8.66 against 12.25 ms);
+    // below 64 k samples a 16-lane team per sample (at 2048 3.08 ms, but 9.77
+    // in contact, where the four samples of a wave take turns; one lane per
+    // sample fills too few waves: at 32 k it is 1.5 x slower); from 64 k on one
+    // lane per sample has the highest throughput
     if (K <= 1024) return MAP_SPLIT;
     if (K <= 2048) return MAP_WAVE;
     return K >= 65536 ? MAP_LANE : MAP_TEAM;
