@@ -608,22 +608,29 @@ static int qp_matrix(mppi_ctx *ctx, int H, double rho, hipStream_t stream, const
         }
         // work queued on this stream may still read the previous matrix
         HIPCHK(hipStreamSynchronize(stream));
+        ctx->qp_H = 0;  // until the new one is whole
         HIPCHK(hipMemcpy(dp, D.data(), dbl, hipMemcpyHostToDevice));
         HIPCHK(hipMemcpy((char *)dp + dbl, P.data(), P.size() * sizeof(float), hipMemcpyHostToDevice));
         ctx->qp_H = H;
         ctx->qp_rho = rho;
         ctx->qp_S = st;
+        double big = 0.0;  // positive definite: the largest entry is on the diagonal
+        for (int i = 0; i < H; ++i) big = std::max(big, D[(size_t)i * H + i]);
+        ctx->qp_unit = std::exp2(std::ceil(std::log2(big)) - 15.0);
     }
     *out = (const float *)((const char *)dp + dbl);
     *S = st;
     return MPPI_OK;
 }
 
-static void qp_args(ProjectArgs &pa, const mppi_scene *scene, const mppi_qp *qp, const float *P, int S, int K, int H)
+static void qp_args(ProjectArgs &pa, const mppi_ctx *ctx, const mppi_scene *scene, const mppi_qp *qp, const float *P,
+                    int S, int K, int H)
 {
     const double dt = scene->host.h * scene->host.n_sub;
     pa.P = P;
     pa.rhoP = (const double *)P - (size_t)H * H;
+    pa.p_unit = ctx->qp_unit;
+    pa.p_unit32 = (float)ctx->qp_unit;
     pa.S = S;
     pa.K = K;
     pa.H = H;
@@ -768,7 +775,7 @@ static int plan_impl(mppi_ctx *ctx, const mppi_scene *scene, const float *x0, co
             if (qp) {
                 // this iteration's samples, projected, then rolled out as given
                 ProjectArgs pa = {};
-                qp_args(pa, scene, qp, dP, qpS, K, H);
+                qp_args(pa, ctx, scene, qp, dP, qpS, K, H);
                 pa.U_out = (float *)dqu;
                 pa.x0 = (const float *)dx0;
                 pa.x0_shared = 1;
@@ -1196,7 +1203,7 @@ int mppi_project(mppi_ctx *ctx, const mppi_scene *scene, const float *X0, int x0
     void *dout;
     if ((rc = out_ptr(ctx, S_OUT0, U_out, nu_n * sizeof(float), dev, &dout))) return rc;
     ProjectArgs pa = {};
-    qp_args(pa, scene, qp, dP, S, K, H);
+    qp_args(pa, ctx, scene, qp, dP, S, K, H);
     pa.U_in = (const float *)dU;
     pa.U_out = (float *)dout;
     pa.x0 = (const float *)dx0;

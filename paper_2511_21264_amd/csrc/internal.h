@@ -101,6 +101,7 @@ struct mppi_ctx {
     int qp_H = 0;
     double qp_rho = 0.0;
     int qp_S = 0;
+    double qp_unit = 0.0;  // 2^-15 of rho times its largest entry rounded up to a power of 2
 };
 
 struct mppi_scene {

@@ -102,11 +102,13 @@ void launch_rollout_batch(const RolloutArgs *d_tab, const int *d_blk, int nblk, 
 void launch_stats_batch(const StatsArgs *d_tab, int n, int m, hipStream_t s);
 void launch_update_batch(const UpdateArgs *d_tab, const int *d_blk, int nblk, int m, hipStream_t s);
 void launch_stats(const StatsArgs &a, hipStream_t s);
-// QP smoothing of sampled sequences (one workgroup per sample, one wave per
-// joint, one horizon step per lane; H <= 64)
+// QP smoothing of sampled sequences, H <= 128: one workgroup per sample (one
+// wave per joint), or from some sample count on one wave per sixteen sequences
 struct ProjectArgs {
     const float *P;         // [H][S] (I + rho A^T A)^-1, rows padded with zeros to S floats
     const double *rhoP;     // [H][H] rho times the same, in double (right before P)
+    double p_unit;          // 2^-15 of rhoP's largest entry rounded up to a power of 2
+    float p_unit32;         // the same
     int S;                  // row stride of P: a multiple of 4, >= H rounded up to 4
     const float *U_in;      // [K][H][14] samples, or null: nu + sigma * z from the Philox counters
     float *U_out;           // [K][H][14] projected samples

@@ -307,32 +307,54 @@ __global__ void __launch_bounds__(14 * 64) project_kernel(ProjectArgs a)
 // groups, and the right-hand side of a column step (step i of every group) is
 // already an MFMA's B operand.  Nothing passes between waves, so there is no
 // barrier.
-//   The product is formed in bf16 MFMAs 16x16x32 from three parts of each
-// factor (24 bits and more: P's parts come from double), six partial products,
-// accumulated in FP32.  An FP32 MFMA and vector instructions do not overlap
-// here, not even from two waves (4 NB^2 MFMAs of 32 cycles came on top of the
-// rest: 152 us), the bf16 ones do: 114 us.  Its error and the scans' against
-// FP64 over the whole iteration is smaller than the FP32 form's: 4.9e-6 of the
-// result's norm against 5.6e-6 at H = 64, 5.6e-6 against 6.8e-6 at H = 128
-// (the block offsets in double bring it from 6.9e-6 and 9.7e-6, for 13 %).
-// Bound by vector instructions, about 50 a step and iteration, at one wave per
+//   The product is formed in fp16 MFMAs 16x16x32 from three parts of each
+// factor: whole units of 2^-9 of the largest magnitude (P's of the matrix, the
+// right-hand side's of the sequence, rounded up to a power of two), then twice
+// 11 bits of what is left (P's from double).  Where position bounds hold, the
+// right-hand side is the suffix sums of hundreds of units that P all but
+// cancels, and an MFMA drops what lies below 2^-24 of the largest of eight
+// products, always downwards: an error that all steps of a sequence share and
+// the iteration sums up.  The products of the whole units are free of it:
+// |row of P| <= 23 of its largest entries in sum (P's norm is at most four of
+// them), so they stay below 2^23 units, and they have a sum of their own.
+// The other five partial products, 2^-10 and less of these, share one.  An
+// FP32 MFMA and vector instructions do not overlap here, not even from two
+// waves (with the product in FP32: 152 us).
+//   Error over the whole iteration against FP64, of the result's norm, the
+// workgroup form's in brackets: 3.2e-6 (5.5e-6) at H = 64, 4.4e-6 (7.1e-6) at
+// H = 128 with the default bounds; with bounds 0.05 rad away, held by most
+// sequences, 2.7e-6 (8.1e-6) and 8.7e-6 (3.1e-5) at rho = 3, 3.8e-6 (4.9e-4)
+// at rho = 1, H = 128.  Three bf16 parts in one sum: 1.9e-5 and 1.7e-4 at
+// rho = 3 (127 us).  The block offsets of the scans are in double (without:
+// half as much again of the error, 13 % of the time).
+//   Bound by vector instructions, about 56 a step and iteration, at one wave per
 // SIMD (K = 1024: 896 waves).  K = 1024, H = 64, 60 iterations: 250 us (a
-// workgroup per sample) -> 130 us; K = 4096: 986 -> 356 us; K = 1024, H = 24:
-// 240 -> 69 us; K = 1024, H = 100: 583 -> 289 us.  P's parts are in LDS in
-// operand order, 24 KB at H = 64 and 96 KB at H = 128 for a workgroup of four
-// waves.
-// two floats as three bf16 parts each, rounded to nearest; the parts' sums are
-// the floats exactly (up to denormals)
-typedef __bf16 h2 __attribute__((ext_vector_type(2)));
+// workgroup per sample) -> 134 us; K = 4096: 987 -> 368 us; K = 1024, H = 24:
+// 241 -> 71 us, H = 100: 583 -> 315 us, H = 128: 586 -> 392 us.  P's parts are
+// in LDS in operand order, 24 KB at H = 64 and 96 KB at H = 128 for a workgroup
+// of four waves.
+// two floats (whole units up to 512 and what is left) as three fp16 parts each
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef float f2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ void split3(float x0, float x1, uint32_t p[3])
 {
+    float y0 = rintf(x0), y1 = rintf(x1);
 #pragma unroll
     for (int t = 0; t < 3; ++t) {
-        p[t] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{x0, x1}, h2));
-        x0 -= __uint_as_float(p[t] << 16);
-        x1 -= __uint_as_float(p[t] & 0xffff0000u);
+        const h2 h = __builtin_convertvector(t == 0 ? f2{y0, y1} : f2{x0, x1}, h2);
+        p[t] = __builtin_bit_cast(uint32_t, h);
+        x0 -= t == 0 ? y0 : (float)h.x;
+        x1 -= t == 0 ? y1 : (float)h.y;
     }
+}
+
+// largest of the four lanes l, l + 16, l + 32, l + 48 (x >= 0), on all of them
+__device__ __forceinline__ uint32_t groups_max(float x)
+{
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    const uint32_t m = max((uint32_t)h[0], (uint32_t)h[1]);
+    const auto g = __builtin_amdgcn_permlane16_swap(m, m, false, false);
+    return max((uint32_t)g[0], (uint32_t)g[1]);
 }
 
 template <int NB, bool FULL>
@@ -340,7 +362,7 @@ __global__ void __launch_bounds__(256, NB <= 4 ? 2 : 1) project_tile_kernel(Proj
 {
     constexpr int R = 4 * NB;
     constexpr int KS = (R + 7) / 8;  // product steps of eight columns a group
-    typedef __bf16 h8 __attribute__((ext_vector_type(8)));
+    typedef _Float16 h8 __attribute__((ext_vector_type(8)));
     typedef float f4 __attribute__((ext_vector_type(4)));
     extern __shared__ __align__(16) unsigned short PA[];  // [row block][product step][part][lane][8]
     const int H = a.H;
@@ -348,10 +370,10 @@ __global__ void __launch_bounds__(256, NB <= 4 ? 2 : 1) project_tile_kernel(Proj
         const int c = e & 7, l = (e >> 3) & 63, w = e >> 9;
         const int rb = w / KS, i = 8 * (w % KS) + c;
         const int row = R * ((l & 15) >> 2) + 4 * rb + (l & 3), col = R * (l >> 4) + i;
-        double p = (i < R && row < H && col < H) ? a.rhoP[row * H + col] : 0.0;
+        double p = (i < R && row < H && col < H) ? a.rhoP[row * H + col] / a.p_unit : 0.0;
 #pragma unroll
         for (int t = 0; t < 3; ++t) {
-            const __bf16 b = (__bf16)(float)p;
+            const _Float16 b = (_Float16)(float)(t == 0 ? 64.0 * rint(p / 64.0) : p);
             PA[((w * 3 + t) * 64 + l) * 8 + c] = __builtin_bit_cast(unsigned short, b);
             p -= (double)(float)b;
         }
@@ -536,7 +558,13 @@ __global__ void __launch_bounds__(256, NB <= 4 ? 2 : 1) project_tile_kernel(Proj
         // next block (the scheduling fences keep it there): one wave per SIMD
         // has nothing else to run under them.  What waits for the other groups
         // (the first two steps' differences, the prefix sums) comes last.
-        // the parts of the right-hand side as MFMA operands, eight steps each
+        // the parts of the right-hand side as MFMA operands, eight steps each, in
+        // units of 2^-9 of the sequence's largest element rounded up to a power of 2
+        float rm = 0.f;
+#pragma unroll
+        for (int i = 0; i < R; i += 2) rm = fmaxf(fmaxf(fabsf(r[i]), fabsf(r[i + 1])), rm);
+        const uint32_t eb = max(groups_max(rm) & 0x7f800000u, 40u << 23);
+        const float per_unit = __uint_as_float((262u << 23) - eb), unit = a.p_unit32 * __uint_as_float(eb - (8u << 23));
         union Op {
             uint32_t u[4];
             h8 h;
@@ -544,14 +572,14 @@ __global__ void __launch_bounds__(256, NB <= 4 ? 2 : 1) project_tile_kernel(Proj
 #pragma unroll
         for (int i = 0; i < 8 * KS; i += 2) {
             uint32_t x[3] = {0u, 0u, 0u};
-            if (i < R) split3(r[i < R ? i : 0], r[i < R ? i + 1 : 0], x);
+            if (i < R) split3(per_unit * r[i < R ? i : 0], per_unit * r[i < R ? i + 1 : 0], x);
 #pragma unroll
             for (int t = 0; t < 3; ++t) rp[i >> 3][t].u[(i & 7) >> 1] = x[t];
         }
         f4 acc[NB];
         auto piece = [&](int p) {  // row kind p % 4 of step p / 4 (0: the step itself)
             const int i = p >> 2;
-            if ((p & 3) == 0) v[i] = vt[i] + acc[i >> 2][i & 3];
+            if ((p & 3) == 0) v[i] = fmaf(unit, acc[i >> 2][i & 3], vt[i]);
             if ((p & 3) == 1) put(0, i, relax(0, i, v[i]));
             if ((p & 3) == 2 && i >= 1) put(1, i, relax(1, i, diff1(v, i, 0.f)));
             if ((p & 3) == 3 && i >= 2) put(2, i, relax(2, i, diff2(v, i, 0.f, 0.f)));
@@ -560,16 +588,27 @@ __global__ void __launch_bounds__(256, NB <= 4 ? 2 : 1) project_tile_kernel(Proj
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             acc[b] = f4{0.f, 0.f, 0.f, 0.f};
+            f4 lo = acc[b];
+            // the six leading products of the parts, the exact ones (0, 0) apart, the
+            // others small ones first; at NB = 8 one product step after another,
+            // with that step's parts alone in registers (428 us otherwise, 391 so)
+            constexpr int TP[6] = {0, 2, 1, 0, 1, 0}, TR[6] = {2, 0, 1, 1, 0, 0};
+            constexpr bool INNER = NB == 8;
             h8 pa[KS][3];
-#pragma unroll
-            for (int k = 0; k < KS; ++k)
+            auto fetch = [&](int k) {
 #pragma unroll
                 for (int t = 0; t < 3; ++t) pa[k][t] = P8[64 * ((b * KS + k) * 3 + t)];
-            // the six leading products of the parts, small ones first
-            constexpr int TP[6] = {0, 2, 1, 0, 1, 0}, TR[6] = {2, 0, 1, 1, 0, 0};
+            };
+            if (!INNER) {
+#pragma unroll
+                for (int k = 0; k < KS; ++k) fetch(k);
+            }
 #pragma unroll
             for (int e = 0; e < 6 * KS; ++e) {
-                acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa[e % KS][TP[e / KS]], rp[e % KS][TR[e / KS]].h, acc[b], 0, 0, 0);
+                const int k = INNER ? e / 6 : e % KS, n = INNER ? e % 6 : e / KS;
+                if (INNER && n == 0) fetch(k);
+                f4 &d = n < 5 ? lo : acc[b];
+                d = __builtin_amdgcn_mfma_f32_16x16x32_f16(pa[k][TP[n]], rp[k][TR[n]].h, d, 0, 0, 0);
                 if (b > 0) {
 #pragma unroll
                     for (int p = PP * e; p < PP * (e + 1); ++p)
@@ -577,6 +616,7 @@ __global__ void __launch_bounds__(256, NB <= 4 ? 2 : 1) project_tile_kernel(Proj
                     if (PP * e < 16) __builtin_amdgcn_sched_barrier(0);
                 }
             }
+            acc[b] += lo;
         }
 #pragma unroll
         for (int n = 0; n < 16; ++n) piece(16 * (NB - 1) + n);
@@ -621,14 +661,14 @@ static void launch_tile(const ProjectArgs &a, hipStream_t s)
         hipLaunchKernelGGL((project_tile_kernel<NB, false>), dim3(grid), dim3(256), lds, s, a);
 }
 
-// The workgroup-per-sample form takes about 66 us (H <= 64) or 150 us (beyond)
-// for every 256 samples, one workgroup a CU; the tile form 69, 130, 285 and
-// 318 us at H = 24, 64, 100 and 128 for up to 1170 samples (a wave a SIMD) and
+// The workgroup-per-sample form takes about 62 us (H <= 64) or 146 us (beyond)
+// for every 256 samples, one workgroup a CU; the tile form 71, 134, 311 and
+// 387 us at H = 24, 64, 100 and 128 for up to 1170 samples (a wave a SIMD) and
 // as much again for the next.  So the tile form is taken from the sample count
-// on at which it is the faster: 257 samples up to H = 32, 513 beyond
-// (K = 513..768: 198 against 130 us at H = 64, 443 against 318 at H = 128).
-// Up to H = 16 the other form's FP32 product is the more exact one (2.1e-6
-// against 2.6e-6 of the result's norm at H = 8), and stays.
+// on at which it is the faster: 257 samples up to H = 32 (122 against 71 us),
+// 513 beyond (K = 600: 188 against 133 us at H = 64, 439 against 387 at
+// H = 128).  Up to H = 16 the other form stays (an earlier product of this one
+// was less exact there, 2.6e-6 against 2.1e-6 of the result's norm at H = 8).
 void launch_project(const ProjectArgs &a, hipStream_t s)
 {
     if (a.H > 16 && a.K > (a.H <= 32 ? 256 : 512)) {
