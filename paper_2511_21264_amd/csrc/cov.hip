@@ -581,11 +581,30 @@ __global__ void __launch_bounds__(256) sample_full_kernel(SampleFullArgs a)
     const int i = 16 * ib + r;
     if (i >= n) return;
     const float nui = a.nu[i];
+    unsigned again = 0u;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int ja = j0 + 4 * q + e;
         if (ja < K) a.U[(long)ja * n + i] = fminf(fmaxf(nui + c0[e], -a.u_max), a.u_max);
         if (ja + 16 < K) a.U[(long)(ja + 16) * n + i] = fminf(fmaxf(nui + c1[e], -a.u_max), a.u_max);
+        again |= (isfinite(c0[e]) ? 0u : 1u << e) | (isfinite(c1[e]) ? 0u : 16u << e);
+    }
+    // The parts of an entry that is infinite in single precision are no sum (Inf,
+    // NaN, NaN): such a row's sums are formed again from L itself, so that they
+    // saturate by their sign.  From the diagonal on, for a factor that failed is
+    // NaN from there.
+    for (; again != 0u; again &= again - 1u) {
+        const int e = __builtin_ctz(again), ja = j0 + 4 * q + (e & 3) + 4 * (e & 4);
+        if (ja >= K) continue;
+        float sum = 0.f;
+        for (int p = i; p >= 0 && sum == sum; --p) {
+            const long z = (((long)(ja >> 4) * nc + (p >> 5)) * 192 + 16 * ((p & 31) >> 3) + (ja & 15)) * 8 + (p & 7);
+            float zp = 0.f;  // the parts' sum is the normal exactly
+#pragma unroll
+            for (int t = 0; t < 3; ++t) zp += __uint_as_float((uint32_t)a.Z[z + 512 * t] << 16);
+            sum = fmaf(zp, (float)a.L[(long)i * n + p], sum);
+        }
+        a.U[(long)ja * n + i] = fminf(fmaxf(nui + sum, -a.u_max), a.u_max);
     }
 }
 
