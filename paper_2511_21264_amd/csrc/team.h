@@ -1372,7 +1372,9 @@ __device__ inline int team_contacts(const DevModel &md, const TeamCtx &tc, const
             const float phi = pb.z - tc.hd[HD_RAD + 8];
             const int nc = min(phi < 0.f ? 1 : 0, md.n_cmax);
             if (tc.li == 0) {
-                if (phi <= 0.f && md.n_cmax > 0) {
+                // counted as the sweeps count: a whole wave whatever the list holds, a team
+                // while there is room (a list always has storage for one)
+                if (phi <= 0.f && (G == 64 || md.n_cmax > 0)) {
                     ++cnt.np_tests;
                     tc.LL.at(0, 0) = __int_as_float(G_BALL);
                     tc.LL.at(0, 1) = __int_as_float(G_TABLE);
