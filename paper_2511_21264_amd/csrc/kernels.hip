@@ -463,6 +463,27 @@ __device__ __forceinline__ void split_put_ball(float *SA, const TeamState &S, V3
     if (TASK) o[3] = make_float4(S.quat[0], S.quat[1], S.quat[2], S.quat[3]);
 }
 
+// Which of the two waves is which is decided by the SIMDs they sit on, so that
+// a SIMD that holds two holds one of each kind.  A CU hands its SIMDs out in
+// the order 0, 2, 1, 3, 0 .. and a workgroup's second wave goes to the next one:
+// with wave 0 the dynamics wave every SIMD then gets one of each, except that
+// some launches (after another kernel has run, mostly a call's first) put one
+// workgroup of one CU the other way round.  Two dynamics waves on one SIMD take
+// turns in their solves, and those two samples end last: the first pass of a
+// plan of the tray-moving phase, K = 1024, H = 64, took 4.75 ms, a repeated one
+// 3.9.  So the wave whose successor in that order is the other one is the
+// dynamics wave.
+__device__ __forceinline__ bool split_geo(float *lds)
+{
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int simd = __builtin_amdgcn_s_getreg(4 | (4 << 6) | (1 << 11));  // HW_ID, bits 4..5
+    if ((threadIdx.x & 63) == 0) lds[wave] = __int_as_float(simd);
+    __syncthreads();
+    const int other = __builtin_amdgcn_readfirstlane(__float_as_int(lds[1 - wave]));
+    const bool first = ((0x1E >> (2 * simd)) & 3) == other, second = ((0x1E >> (2 * other)) & 3) == simd;
+    return first || second ? second : wave == 1;
+}
+
 template <int NC, bool TASK = false>
 __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2, 2))) rollout_split_kernel(RolloutArgs a0, const RolloutArgs *tab, const int *blk,
                                                              int m)
@@ -471,12 +492,12 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2, 2))
     RolloutArgs a;
     int bid;
     block_scene(a0, tab, blk, m, a, bid);
-    // a scalar, as are the other conditions that barriers stand under
-    const bool geo = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 1;
     const int lane = threadIdx.x & 63;
     const int row = lane >> 4;
     float *blockD = lds + HD_FIELDS, *blockG = blockD + team_lds_floats(NC);
     float *SA = blockG + team_lds_floats(NC);
+    // a scalar, as are the other conditions that barriers stand under
+    const bool geo = split_geo(SA);
     TeamCtx tc;
     tc.lane = lane;
     tc.t = lane & 15;
