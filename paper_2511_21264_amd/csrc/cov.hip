@@ -192,10 +192,9 @@ void launch_cov_update(const CovArgs &a, hipStream_t s)
     // (K = 256, n = 1400: 30.7 us against 28.3); at 128 samples or fewer four
     // waves have one step each already (K = 64, n = 280: 14.6 us either way).
     if (tiles <= 256 && a.K > 16 * CG) {
-        if (small)
-            hipLaunchKernelGGL((cov_syrk_kernel<8, uint32_t>), dim3(tiles), dim3(512), 0, s, a);
-        else
-            hipLaunchKernelGGL((cov_syrk_kernel<8, long>), dim3(tiles), dim3(512), 0, s, a);
+        // 22 tile rows at most (n <= 704), so K n stays below 2^30 up to K = 2^20
+        static_assert(MPPI_MAX_K <= 1 << 20, "32-bit offsets of the eight-wave form");
+        hipLaunchKernelGGL((cov_syrk_kernel<8, uint32_t>), dim3(tiles), dim3(512), 0, s, a);
     } else {
         if (small)
             hipLaunchKernelGGL((cov_syrk_kernel<4, uint32_t>), dim3(tiles), dim3(256), 0, s, a);

@@ -668,18 +668,6 @@ __device__ __forceinline__ bool team_coarse(const DevModel &md, const float *hd,
     return hit;
 }
 
-// ArmKin of both arms from the published geometry (joint axes are in the park area)
-__device__ __forceinline__ void team_kin_from_lds(const float *tl, ArmKin kin[2])
-{
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int i = 0; i <= NJ; ++i) {
-            const float *p = tl + TG_PTS + 24 * a + 3 * i;
-            kin[a].o[i] = v3(p[0], p[1], p[2]);
-        }
-}
-
 // AABB test of a candidate pair word (ga | gb << 8; geom A is always dynamic)
 // after growing A by margin; the same comparisons as aabb_overlap on the
 // geoms' boxes, against the table the lower z alone.  No branches: geom B's
