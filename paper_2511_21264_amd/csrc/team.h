@@ -78,7 +78,7 @@ constexpr int HD_FIELDS = HD_RAD + 12;
 // blocks G_st (NC x NC x 9), row matrix A (4NC x 4NC), b, 1/(A_rr + R_r), R,
 // and the multipliers when several contacts are active
 constexpr int tcs_fields(int nc) { return 20 * nc + 9 * nc * nc + 16 * nc * nc + 16 * nc; }
-constexpr int PK_FIELDS4 = 100; // park area: both arms' factors
+constexpr int PK_FIELDS4 = 56;  // park area: both arms' factors (2 x 28)
 constexpr int team_lds_floats(int nc) { return TG_FIELDS + nc * CL_FIELDS + PK_FIELDS4 + tcs_fields(nc); }
 // 16-byte alignment of the park and solve areas (float4 reads and writes)
 static_assert(HD_FIELDS % 4 == 0 && TG_FIELDS % 4 == 0 && (4 * CL_FIELDS) % 4 == 0 && PK_L % 4 == 0 &&
