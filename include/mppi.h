@@ -352,7 +352,11 @@ typedef struct mppi_qp {
  *   X0: [K][MPPI_NX] start states (their commanded positions q_des), or one
  *   state for every sample when x0_shared != 0.  flags: MPPI_DEVICE_PTRS,
  *   MPPI_SYNC.  Errors: MPPI_E_INVAL (NULL, K < 1, H < 1 or H > 128, bad qp
- *   values), MPPI_E_NOMEM, MPPI_E_DEVICE. */
+ *   values), MPPI_E_NOMEM, MPPI_E_DEVICE.
+ * The solver has two forms in single precision, which differ by rounding: one
+ * for few samples, and one from K = 257 on for 16 < H <= 32 and from K = 513 on
+ * for H > 32.  Within a form a sequence's result does not depend, bit for bit,
+ * on what it is projected with. */
 int mppi_project(mppi_ctx *ctx, const mppi_scene *scene, const float *X0, int x0_shared, const float *U_in,
                  float *U_out, int K, int H, const mppi_qp *qp, unsigned flags, void *stream);
 
