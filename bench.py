@@ -409,7 +409,7 @@ def bench_qp(mp, ctx, sc, pp, config, plain_ms, n_launch=20, n_plan=5):
         lat.append((time.perf_counter() - a) * 1e3)
     scene.close()
     return {
-        "kernel": "project_kernel",
+        "kernel": "project_tile_kernel",
         "iters": p["iters"], "rho": p["rho"], "alpha": p["alpha"],
         "launch": f"K={K} samples x 14 joints, H={H}",
         "project_ms_per_launch": launch_ms,
@@ -1122,15 +1122,17 @@ def summarize_next(base, meta):
                        "order by total_duration desc").fetchall()
     K, H, n, iters = 1024, 64, 896, 60
     model = {  # kernel -> (flops per launch, peak, label)
-        "project_kernel": (K * 14 * iters * 2.0 * H * H, PEAK_FP32, "FP32 (product with P only)"),
+        "project_tile_kernel": (K * 14 * iters * 2.0 * H * H, PEAK_FP32,
+                                "FP32 (product with P only, which runs as six fp16 products)"),
         "cov_syrk_kernel": (float(K) * n * (n + 1), PEAK_FP64, "FP64 MFMA"),
-        "sample_full_kernel": (float(K) * n * (n + 1), PEAK_FP32, "FP32 MFMA"),
+        "sample_full_kernel": (float(K) * n * (n + 1), PEAK_FP32, "FP32; runs as six bf16 products"),
     }
     # algorithmic HBM bytes per launch: inputs read once, outputs written once
     alg_bytes = {
-        "project_kernel": K * H * 14 * 4 * 2 + H * (H + 4) * 4,   # samples in and out, P
+        "project_tile_kernel": K * H * 14 * 4 * 2 + H * H * 8,   # samples in and out, P
         "cov_syrk_kernel": K * n * 4 + K * 8 + n * 8 + 2 * n * n * 8,  # samples, weights, mean, Sigma in and out
-        "sample_full_kernel": 2 * K * n * 4 + n * n * 4 // 2,    # normals in, samples out, lower factor
+        # normals and lower factor in (three bf16 parts each), samples out
+        "sample_full_kernel": K * n * (6 + 4) + n * n * 6 // 2,
         "chol_step_kernel": None, "chol_diag_kernel": None,
     }
 
@@ -1156,7 +1158,7 @@ def summarize_next(base, meta):
            "|---|---|---|---|---|---|---|---|"]
     for name, calls, tot, avg in rows:
         short = name.split("(")[0].replace("mppi::", "").replace("void ", "")
-        short = short.split("<")[0] if short.startswith("project_kernel") else short
+        short = short.split("<")[0] if short.startswith(("project_", "cov_syrk_")) else short
         if short.startswith(("rollout", "stats", "update", "reset", "at::", "__amd")):
             continue
         key = next((k for k in fetch if k.split("<")[0] == short), None)

@@ -352,9 +352,11 @@ int scene_mapping(const mppi_ctx *c, const mppi_scene *s, long K, unsigned flags
             return fail(MPPI_E_INVAL, "scenes with a box object or the further task-cost terms run one lane, one "
                                       "wave or two waves per sample, not four samples a wave");
         // unpinned: one lane per sample from 16 k samples on (the task forms
-        // have no four-samples-a-wave form: at 32 k samples one lane per
-        // sample runs 1.5 x faster than a wave per sample), else the wave or
-        // split form that the ball scenes get for K
+        // have no four-samples-a-wave form; a wave per sample against a lane,
+        // H = 32, tray move and hand-over pick: 15.9 and 19.4, 16.8 and 23.0 ms
+        // at 12288 samples, 20.9 and 19.9, 21.8 and 23.1 at 16384, 41.1 and
+        // 23.3, 42.5 and 27.0 at 32768), else the wave or split form that the
+        // ball scenes get for K
         int m = pinned;
         if (m == MAP_AUTO) m = K >= 16384 ? MAP_LANE : resolve_mapping(c, K, flags);
         *map = m == MAP_LANE ? MAP_TASK : m == MAP_SPLIT ? MAP_TASK_SPLIT : MAP_TASK_WAVE;

@@ -5,7 +5,7 @@
 //
 //   cov_syrk_kernel    Sigma' = (1 - eta) Sigma + eta sum_j w_j D_j D_j^T / sum w
 //                      + eps I with D_j = u_j - nu_{m+1}: one workgroup per
-//                      32 x 32 lower tile, the four waves split the samples,
+//                      32 x 32 lower tile, four or eight waves split the samples,
 //                      FP64 MFMA 16x16x4 with the deviation and the weight
 //                      formed in the operand load; each symmetric pair is
 //                      written by one lane (so the update may run in place)

@@ -376,22 +376,23 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) ro
     }
 }
 
-// Split mapping: two waves per sample, which share the critical path.  Wave 0
+// Split mapping: two waves per sample, which share the critical path.  One
 // (dynamics) owns the arms: inertia, factorisation, bias forces and free
 // velocities, then their integration and the kinematics at the new positions.
-// Wave 1 (geometry) owns the ball: meanwhile it runs the geom AABBs and the
+// The other (geometry) owns the ball: meanwhile it runs the geom AABBs and the
 // contact sweep on the kinematics, the ball's contact and integration, and
 // once per control step the cost of the previous one.  Barriers per substep:
-//   B1  the positions and kinematics are in LDS, for wave 1;
-//   B2  the contact list is in LDS, for wave 0.  Wave 0 meets it within the
+//   B1  the positions and kinematics are in LDS, for the geometry wave;
+//   B2  the contact list is in LDS, for the dynamics wave, which meets it within the
 //       dynamics, about where the coarse test ends, or, if that test had found
 //       something near in the substep before (so the sweep ran), after them;
-//   B3  only where an arm is in contact: wave 0 has solved the contacts with
+//   B3  only where an arm is in contact: the dynamics wave has solved them with
 //       the ball's free velocities and hands back the final ones.
 // Both waves decide on the same values in LDS, so they meet every barrier the
 // same number of times.  Every value equals the wave-per-sample mapping's bit
 // for bit.
-// A substep of a ball on the table takes 6.2 k cycles (dynamics 2.2 k to B2,
+// A substep of a ball on the table takes 6.2 k cycles (by clock reads between
+// its parts: dynamics 2.2 k to B2,
 // 1.2 k after, kinematics 1.7 k, handoff 0.6 k; sweep 1.7-2.1 k, ball 2.8 k)
 // where the dynamics wave alone did the ball's step too and the other waited,
 // 8.1 k.  One control step of one sample 42.4 -> 34.0 us; K = 64, H = 20 five
@@ -399,12 +400,12 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) ro
 // holds a wave of each kind of two samples and the slowest samples, with arms
 // in contact (12 k cycles), set the end, so both their waves issue ahead.
 // state handoff (SA): q[14], contact count (SA_NC, 0 where the arms are free),
-// finite flag (SA_BAD); for the solve of wave 0 the ball's centre and free
-// velocities (SA_BALL), which it replaces with the final ones, and the
-// object's quaternion; for the task form's cost qd[14]; the kinematics of the
-// team's 16 lanes, 20 floats each (a, z, o, o1, and the link frame's x, y)
+// finite flag (SA_BAD); for the dynamics wave's solve the ball's centre and free
+// velocities and the object's quaternion (SA_BALL), and the final velocities in
+// return (SA_OUT); for the task form's cost qd[14]; the kinematics of the team's
+// 16 lanes, 20 floats each (a, z, o, o1, and the link frame's x, y)
 constexpr int SPLIT_LATE = 256;  // flag beside the contact count: the sweep ran, meet B2 late next time
-constexpr int SA_NC = 14, SA_BAD = 15, SA_BALL = 16, SA_QUAT = 28, SA_QD = 32, SA_OUT = 46, SA_KIN = 52, SPLIT_SA = SA_KIN + 16 * 20;
+constexpr int SA_NC = 14, SA_BAD = 15, SA_BALL = 16, SA_QD = 32, SA_OUT = 46, SA_KIN = 52, SPLIT_SA = SA_KIN + 16 * 20;
 
 // FRAME: with the link frame's x and y axes
 template <bool FRAME>
@@ -710,9 +711,13 @@ int pick_mapping(int K, int requested)
     // ~2 samples per SIMD one wave per sample (at 1100: 3.56 against 3.53 and
     // 8.27 against 9.47, at 2048 3.61 against 4.63 and 8.66 against 12.25 ms);
     // below 64 k samples a 16-lane team per sample (at 2048 3.08 ms, but 9.77
-    // in contact, where the four samples of a wave take turns; one lane per
-    // sample fills too few waves: at 32 k it is 1.5 x slower); from 64 k on one
-    // lane per sample has the highest throughput
+    // in contact, where the four samples of a wave take turns); from 64 k on one
+    // lane per sample.  One iteration at H = 64, team against lane: 4.1 and 5.9 ms
+    // at 16384 samples, 11.9 and 19.1 in contact; 5.9 and 6.1, 17.3 and 20.2 at
+    // 24576; 7.7 and 6.4, 22.7 and 23.6 at 32768; 9.5 and 6.6, 27.9 and 24.9 at
+    // 40000; 14.8 and 7.5, 44.0 and 27.5 at 65535.  So the two cross between
+    // 25000 and 35000 samples; the line stays above that because the lane form
+    // rounds differently: plans of those sizes keep their results
     if (K <= 1024) return MAP_SPLIT;
     if (K <= 2048) return MAP_WAVE;
     return K >= 65536 ? MAP_LANE : MAP_TEAM;

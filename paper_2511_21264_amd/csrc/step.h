@@ -600,7 +600,7 @@ __device__ __forceinline__ void contact_solve(const DevModel &md, const ArmKin k
 // scalar registers.  Everything else is inlined: as a call, the substep took
 // its state and the model through memory.  With that and the rolled, bounded
 // sweeps a launch of K = 65536, H = 64 went from 22.0 to 8.1 ms (14.1 with the
-// sweeps alone).
+// sweeps alone; 7.5 to 10 ms over cards and their sustained clocks).
 template <int NC, bool BOX>
 __device__ __attribute__((noinline)) void contact_solve_call(const DevModel *mp, const ArmKin *kin, const LanePark pk,
                                                              V3 pb, const LaneList LL, int nc, float *v, V3 *vb,
