@@ -442,7 +442,12 @@ void launch_cholesky(const CholArgs &a, hipStream_t s)
 // lanes x 8 values (lane l: row l % 16, columns 8 (l / 16) ..), part after
 // part, so a wave reads an operand as one contiguous kilobyte.  Rows past K or
 // n and columns past n are zero; of L only the chunks up to the diagonal exist.
+//
+// L is scaled by 2^32 (and the sums back), so that its third parts stay normal
+// down to entries of 1e-42, where single precision ends; entries past 1e28
+// make a sum infinite, which is then formed again (below).
 typedef __bf16 b8 __attribute__((ext_vector_type(8)));
+constexpr double LS = 4294967296.0;  // 2^32
 
 __device__ __forceinline__ void split3(float x, unsigned short p[3])
 {
@@ -518,7 +523,7 @@ __global__ void __launch_bounds__(256) sample_operands_kernel(SampleFullArgs a, 
     for (int e = 0; e < 8; ++e) {
         const int p = p0 + e;
         if (i < n && p <= i) {
-            double x = a.L[(long)i * n + p];
+            double x = LS * a.L[(long)i * n + p];
 #pragma unroll
             for (int t = 0; t < 3; ++t) {
                 const __bf16 b = (__bf16)(float)x;
@@ -579,13 +584,13 @@ __global__ void __launch_bounds__(256) sample_full_kernel(SampleFullArgs a)
     }
     const int i = 16 * ib + r;
     if (i >= n) return;
-    const float nui = a.nu[i];
+    const float nui = a.nu[i], unscale = (float)(1.0 / LS);
     unsigned again = 0u;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int ja = j0 + 4 * q + e;
-        if (ja < K) a.U[(long)ja * n + i] = fminf(fmaxf(nui + c0[e], -a.u_max), a.u_max);
-        if (ja + 16 < K) a.U[(long)(ja + 16) * n + i] = fminf(fmaxf(nui + c1[e], -a.u_max), a.u_max);
+        if (ja < K) a.U[(long)ja * n + i] = fminf(fmaxf(fmaf(unscale, c0[e], nui), -a.u_max), a.u_max);
+        if (ja + 16 < K) a.U[(long)(ja + 16) * n + i] = fminf(fmaxf(fmaf(unscale, c1[e], nui), -a.u_max), a.u_max);
         again |= (isfinite(c0[e]) ? 0u : 1u << e) | (isfinite(c1[e]) ? 0u : 16u << e);
     }
     // The parts of an entry that is infinite in single precision are no sum (Inf,
@@ -595,15 +600,15 @@ __global__ void __launch_bounds__(256) sample_full_kernel(SampleFullArgs a)
     for (; again != 0u; again &= again - 1u) {
         const int e = __builtin_ctz(again), ja = j0 + 4 * q + (e & 3) + 4 * (e & 4);
         if (ja >= K) continue;
-        float sum = 0.f;
+        double sum = 0.0;
         for (int p = i; p >= 0 && sum == sum; --p) {
             const long z = (((long)(ja >> 4) * nc + (p >> 5)) * 192 + 16 * ((p & 31) >> 3) + (ja & 15)) * 8 + (p & 7);
             float zp = 0.f;  // the parts' sum is the normal exactly
 #pragma unroll
             for (int t = 0; t < 3; ++t) zp += __uint_as_float((uint32_t)a.Z[z + 512 * t] << 16);
-            sum = fmaf(zp, (float)a.L[(long)i * n + p], sum);
+            sum = fma((double)zp, (double)(float)a.L[(long)i * n + p], sum);
         }
-        a.U[(long)ja * n + i] = fminf(fmaxf(nui + sum, -a.u_max), a.u_max);
+        a.U[(long)ja * n + i] = fminf(fmaxf(nui + (float)sum, -a.u_max), a.u_max);
     }
 }
 
