@@ -432,10 +432,14 @@ void launch_cholesky(const CholArgs &a, hipStream_t s)
 // U = clip(nu + Z L^T) with Z (K x n normals) and L (n x n, lower) split into
 // three bf16 parts each (24 bits and more; L's from double), the product as
 // six bf16 partial products accumulated in FP32: 2.7 times the FP32 matrix
-// rate, and closer to FP64 than with L rounded to FP32 (2.7e-7 of the result's
-// norm against 3.2e-7).  Two launches instead of four (conversion of L,
+// rate, and closer to FP64 than with L rounded to FP32 (1.9e-7 of the result's
+// norm against 3.2e-7).  What an MFMA drops (below 2^-24 of the largest of eight
+// products) it drops downwards, so the odd chunks of L are negated and have
+// sums of their own, which are subtracted: with one sum 2.7e-7, and all samples
+// shifted by -2.3e-8 of their standard deviation (now -4e-9; 24.5 -> 24.9 us).
+// Two launches instead of four (conversion of L,
 // clearing of its upper triangle, normals, product): K = 1024, n = 896 39.8 ->
-// 24.6 us, K = 4096, n = 1400 184 -> 99 us; what is left is the operands' way
+// 24.9 us, K = 4096, n = 1400 184 -> 99 us; what is left is the operands' way
 // from the L2 (three chunks ahead; one ahead 29.9 us), not the products' 2 us.
 //
 // Both are laid out as MFMA 16x16x32 operands: 16 rows x 32 columns are 64
@@ -523,7 +527,7 @@ __global__ void __launch_bounds__(256) sample_operands_kernel(SampleFullArgs a, 
     for (int e = 0; e < 8; ++e) {
         const int p = p0 + e;
         if (i < n && p <= i) {
-            double x = LS * a.L[(long)i * n + p];
+            double x = (c & 1 ? -LS : LS) * a.L[(long)i * n + p];
 #pragma unroll
             for (int t = 0; t < 3; ++t) {
                 const __bf16 b = (__bf16)(float)x;
@@ -556,7 +560,7 @@ __global__ void __launch_bounds__(256) sample_full_kernel(SampleFullArgs a)
     const b8 *z0 = reinterpret_cast<const b8 *>(a.Z) + (long)(2 * jt) * nc * 192 + lane;
     const b8 *z1 = z0 + (two ? (long)nc * 192 : 0);
     const b8 *lp = reinterpret_cast<const b8 *>(a.Lp) + (long)ib * nc * 192 + lane;
-    f4 c0 = {0.f, 0.f, 0.f, 0.f}, c1 = c0;
+    f4 c0 = {0.f, 0.f, 0.f, 0.f}, c1 = c0, o0 = c0, o1 = c0;  // even and (negated) odd chunks
     b8 x0[SD][3], x1[SD][3], y[SD][3];
     auto load = [&](int s, int c) {
 #pragma unroll
@@ -568,20 +572,24 @@ __global__ void __launch_bounds__(256) sample_full_kernel(SampleFullArgs a)
     };
 #pragma unroll
     for (int s = 0; s < SD; ++s) load(s, min(s, nch - 1));
-    for (int cb = 0; cb < nch; cb += SD) {
+    for (int cb = 0; cb < nch; cb += 2 * SD) {
 #pragma unroll
-        for (int s = 0; s < SD; ++s) {
-            if (cb + s < nch) {  // uniform over the wave
+        for (int u = 0; u < 2 * SD; ++u) {
+            const int s = u % SD;
+            if (cb + u < nch) {  // uniform over the wave
                 constexpr int TX[6] = {0, 2, 1, 0, 1, 0}, TY[6] = {2, 0, 1, 1, 0, 0};  // small products first
 #pragma unroll
                 for (int e = 0; e < 6; ++e) {
-                    c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x0[s][TX[e]], y[s][TY[e]], c0, 0, 0, 0);
-                    c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x1[s][TX[e]], y[s][TY[e]], c1, 0, 0, 0);
+                    f4 &d0 = u & 1 ? o0 : c0, &d1 = u & 1 ? o1 : c1;
+                    d0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x0[s][TX[e]], y[s][TY[e]], d0, 0, 0, 0);
+                    d1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x1[s][TX[e]], y[s][TY[e]], d1, 0, 0, 0);
                 }
-                load(s, min(cb + s + SD, nch - 1));
+                load(s, min(cb + u + SD, nch - 1));
             }
         }
     }
+    c0 -= o0;
+    c1 -= o1;
     const int i = 16 * ib + r;
     if (i >= n) return;
     const float nui = a.nu[i], unscale = (float)(1.0 / LS);
